@@ -82,7 +82,9 @@ typedef struct {
   int32_t hidden_width;  /* c */
   int32_t hidden_layers; /* H activated layers, followed by the c -> num_outputs output layer */
   int32_t activation;    /* fvsrn_act */
-  int32_t precision;     /* network arithmetic: FVSRN_F32 (FP32 MFMA), FVSRN_F16 or
+  int32_t precision;     /* network arithmetic: FVSRN_F32 (FP32 MFMA; where only
+                            values of a sine network are needed, FP16 MFMA on operands
+                            split into two FP16 values, as accurate), FVSRN_F16 or
                             FVSRN_BF16 (MFMA with FP32 accumulation). Phases, sigmoid,
                             TF and compositing are FP32 always; the latent
                             interpolation too, except for an FP16 or BF16 network on

@@ -14,6 +14,7 @@
 // termination threshold.
 #pragma once
 #include "fvsrn_adjoint.hpp"
+#include "fvsrn_split.hpp"
 
 namespace fvsrn_detail {
 
@@ -22,6 +23,15 @@ namespace {
 // Shading modes of the render kernel: none, forward-mode gradient, central
 // differences, the network's predicted gradient, the adjoint (Sec. 6).
 enum { kShadeNone = 0, kShadeFwd = 1, kShadeFD = 2, kShadePred = 3, kShadeAdj = 4 };
+
+// FP32 sine networks with the octave features evaluate on the FP16 matrix
+// cores (fvsrn_split.hpp) wherever only values are needed; forward-mode
+// tangents and the adjoint's deltas have no bound that the split could rely
+// on and stay on the FP32 MFMA, as do the other activations.
+template <class CF, int MODE>
+constexpr bool use_split() {
+  return CF::P == kF32 && CF::ACT == kSine && CF::TE == 0 && !CF::FM && MODE != kShadeFwd && MODE != kShadeAdj;
+}
 
 // Waves per workgroup cap (sets the VGPR budget through the launch bounds):
 // value-mode networks with the packed FP16 latent path fit 4 waves per SIMD
@@ -40,6 +50,7 @@ enum { kShadeNone = 0, kShadeFwd = 1, kShadeFD = 2, kShadePred = 3, kShadeAdj = 
 // registers).
 template <class CF, int MODE, bool POINTS = false>
 constexpr int max_waves() {
+  if (use_split<CF, MODE>()) return 12;
   if (MODE == kShadeAdj) return (CF::P == kF16 && CF::C == 32 && CF::G16) ? 12 : 8;
   if (MODE == kShadeFwd) return (CF::P == kF16 && CF::C <= 48 && CF::G16) ? 12 : 8;
   if (MODE == kShadeFD) {
@@ -68,7 +79,29 @@ constexpr int kLdsBytes = 160 * 1024;
 template <class CF, int MODE>
 __host__ __device__ int fixed_lds_bytes(int H) {
   using G = typename CF::G;
-  return G::weight_bytes(H) + (MODE == kShadeAdj ? G::back_bytes(H) : 0);
+  if constexpr (use_split<CF, MODE>()) return SplitGeo<CF>::weight_bytes(H);
+  else return G::weight_bytes(H) + (MODE == kShadeAdj ? G::back_bytes(H) : 0);
+}
+
+// LDS bytes of one wave's input tile; the split render also keeps its lanes'
+// FP64 rays there, which would cost 18 registers over the MLP.
+constexpr int kRayBytes = 9 * 8 * kWave;
+template <class CF, int MODE, bool POINTS = false>
+constexpr int wave_lds_bytes() {
+  if constexpr (use_split<CF, MODE>()) return SplitGeo<CF>::WAVE_BYTES + (POINTS ? 0 : kRayBytes);
+  else return CF::G::FEAT_BYTES;
+}
+
+// Workgroups of wpb waves and shm bytes of LDS that a CU holds at once, by LDS
+// and by the VGPR budget of max_waves. The CU deals a workgroup's waves out
+// to its four SIMDs from the first one on, so a workgroup of w waves takes
+// ceil(w / 4) of the first SIMD's wave slots: two workgroups of 6 waves do
+// not fit where one of 12 does (measured: the second one waited for the
+// first, 24.7 against 18.8 ms for a 1024^2 view of the FP32 study network).
+template <class CF, int MODE, bool POINTS = false>
+int blocks_per_cu(int wpb, size_t shm) {
+  const int by_lds = (int)(kLdsBytes / shm), by_regs = max_waves<CF, MODE, POINTS>() / 4 / ((wpb + 3) / 4);
+  return by_lds < by_regs ? by_lds : by_regs;
 }
 
 // Waves per workgroup. The VGPR budget of max_waves allows that many waves
@@ -79,14 +112,12 @@ __host__ __device__ int fixed_lds_bytes(int H) {
 // rays (measured: 3 x 4 waves beat 1 x 12 waves by 12% on the BF16 path).
 template <class CF, int MODE, bool POINTS = false>
 int waves_per_block(int H) {
-  using G = typename CF::G;
   constexpr int cap = max_waves<CF, MODE, POINTS>();
   const int wb = fixed_lds_bytes<CF, MODE>(H);
   int best = 0, best_waves = 0;
   for (int w = 1; w <= cap; ++w) {
-    const int per_cu = kLdsBytes / (wb + w * G::FEAT_BYTES);
-    const int waves = per_cu * w < cap ? per_cu * w : cap;
-    if (per_cu >= 1 && waves > best_waves) {
+    const int waves = w * blocks_per_cu<CF, MODE, POINTS>(w, (size_t)wb + w * wave_lds_bytes<CF, MODE, POINTS>());
+    if (waves > best_waves) {
       best = w;
       best_waves = waves;
     }
@@ -94,12 +125,10 @@ int waves_per_block(int H) {
   return best;
 }
 
-// Workgroups of wpb waves and shm bytes of LDS that the GPU holds at once (by
-// LDS and by the VGPR budget of max_waves).
+// Workgroups that the GPU holds at once.
 template <class CF, int MODE, bool POINTS = false>
 long long resident_blocks(int wpb, size_t shm) {
-  const int per_cu_lds = (int)(kLdsBytes / shm), per_cu_regs = max_waves<CF, MODE, POINTS>() / wpb;
-  return (long long)device_cus() * (per_cu_lds < per_cu_regs ? per_cu_lds : per_cu_regs);
+  return (long long)device_cus() * blocks_per_cu<CF, MODE, POINTS>(wpb, shm);
 }
 
 // ----------------------------------------------------- TF, camera, march
@@ -180,7 +209,9 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
   constexpr int LPR = TileShape<MODE>::LPR, TW = TileShape<MODE>::TW;
   constexpr bool ADJ = MODE == kShadeAdj;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  stage_weights<CF>(nd, smem);
+  constexpr bool SPLIT = use_split<CF, MODE>();
+  if constexpr (SPLIT) stage_split<CF>(nd, smem);
+  else stage_weights<CF>(nd, smem);
   char* bsm = smem + G::weight_bytes(nd.H);  // transposed fragments (adjoint)
   if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
   __syncthreads();
@@ -200,8 +231,11 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
                            FD && (q == 5 || q == 6) ? fh : 0.0f};
   const float inv_2h = FD ? 0.5f / m.fd_step : 0.0f;
   const bool fixed = m.fixed_steps > 0;
-  E* feat = reinterpret_cast<E*>(smem + fixed_lds_bytes<CF, MODE>(nd.H) + wave * G::FEAT_BYTES);
+  char* wlds = smem + fixed_lds_bytes<CF, MODE>(nd.H) + wave * wave_lds_bytes<CF, MODE>();
+  E* feat = reinterpret_cast<E*>(wlds);
   E* myrow = feat + lane * G::ROW;
+  SplitTile st = {reinterpret_cast<f4*>(wlds), reinterpret_cast<f4*>(wlds) + kWave};
+  double* lray = reinterpret_cast<double*>(wlds + 2 * kWave * sizeof(f4)) + lane;  // SPLIT: this lane's ray
   unsigned long long n_samp = 0, n_hit = 0, iters = 0;
   for (int tile = next_tile(queue, lane); tile < n_tiles; tile = next_tile(queue, lane)) {
     const int v = tile / tiles_per_view;
@@ -218,6 +252,17 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
     constexpr bool kPosF64 = CF::P == kF32;
     const RayD rayd = make_ray_d(cam, in_img ? px : 0, in_img ? py : 0, vb.width, vb.height, m);
     const Ray ray = round_ray(rayd);
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        lray[a * kWave] = rayd.o[a];
+        lray[(3 + a) * kWave] = rayd.d[a];
+      }
+      lray[6 * kWave] = rayd.t0;
+      lray[7 * kWave] = rayd.t1;
+      lray[8 * kWave] = rayd.ds;
+      wave_lds_sync();
+    }
     bool active = in_img && ray.hit && ray.nseg > 0;
     float tfe[G::TIN > 0 ? G::TIN : 1];  // the view's time inputs (time-encoded networks)
     if constexpr (G::TIN > 0) time_features<CF::TE>(cam.tau, tfe);
@@ -230,7 +275,14 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
     auto sample_at = [&](int ii, bool act, float& sx, float& sy, float& sz, float& len) {
       if constexpr (kPosF64) {
         float pp[3];
-        segment_d(rayd, ii, fixed, fd_off, pp, len);
+        if constexpr (SPLIT) {
+          const RayD r = {{lray[0], lray[kWave], lray[2 * kWave]},
+                          {lray[3 * kWave], lray[4 * kWave], lray[5 * kWave]},
+                          lray[6 * kWave], lray[7 * kWave], lray[8 * kWave], 0, true};
+          segment_d(r, ii, fixed, fd_off, pp, len);
+        } else {
+          segment_d(rayd, ii, fixed, fd_off, pp, len);
+        }
         sx = act ? pp[0] : 0.0f;
         sy = act ? pp[1] : 0.0f;
         sz = act ? pp[2] : 0.0f;
@@ -252,7 +304,8 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
       ++iters;
       float len, sx, sy, sz;
       sample_at(i, active, sx, sy, sz, len);
-      write_features<CF, GRAD>(myrow, ls, role, sx, sy, sz, tfe, nd.fm);
+      if constexpr (SPLIT) st.put(lane, ls, CF::F, sx, sy, sz);
+      else write_features<CF, GRAD>(myrow, ls, role, sx, sy, sz, tfe, nd.fm);
       wave_lds_sync();
       f4 yo;
       float ga[3] = {0.0f, 0.0f, 0.0f};
@@ -261,6 +314,8 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
         yo[0] = mlp_tile_adj<CF, HH>(smem, bsm, feat);
         wave_lds_sync();
         input_vjp<CF>(myrow, ls, sx, sy, sz, ga);
+      } else if constexpr (SPLIT) {
+        yo = mlp_split<CF>(smem, st, ls, nd.H);
       } else {
         yo = mlp_tile<CF, GRAD>(smem, feat, nd.H, role);
       }
@@ -304,7 +359,14 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
       const bool comp = active && len > 0.0f;
       float rgba[4];
       tf_eval(tf, dens, rgba);
-      if (m.phong) phong(rgba, gx, gy, gz, ray.d, m);
+      if (m.phong) {
+        if constexpr (SPLIT) {
+          const float dir[3] = {(float)lray[3 * kWave], (float)lray[4 * kWave], (float)lray[5 * kWave]};
+          phong(rgba, gx, gy, gz, dir, m);
+        } else {
+          phong(rgba, gx, gy, gz, ray.d, m);
+        }
+      }
       composite(acc, rgba, comp ? len : 0.0f);
       i += comp ? 1 : 0;
       active = comp && !(acc.T < m.ert_eps) && i < ray.nseg;
@@ -345,13 +407,17 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
   constexpr bool ADJ = PM == kShadeAdj;
   constexpr int PER = GRAD ? 16 : 64;  // points per wave step
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  stage_weights<CF>(nd, smem);
+  constexpr bool SPLIT = use_split<CF, PM>();
+  if constexpr (SPLIT) stage_split<CF>(nd, smem);
+  else stage_weights<CF>(nd, smem);
   char* bsm = smem + G::weight_bytes(nd.H);
   if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  E* feat = reinterpret_cast<E*>(smem + fixed_lds_bytes<CF, PM>(nd.H) + wave * G::FEAT_BYTES);
+  char* wlds = smem + fixed_lds_bytes<CF, PM>(nd.H) + wave * wave_lds_bytes<CF, PM, true>();
+  E* feat = reinterpret_cast<E*>(wlds);
   E* myrow = feat + lane * G::ROW;
+  SplitTile st = {reinterpret_cast<f4*>(wlds), reinterpret_cast<f4*>(wlds) + kWave};
   const LaneRole role = GRAD ? grad_role(lane & 3) : value_role();
   const LatentSrc ls = make_latent_src(nd, key, key_w);
   float tfe[G::TIN > 0 ? G::TIN : 1];  // time inputs of the evaluation time
@@ -378,7 +444,8 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
     const long long idx = c * PER + (GRAD ? (lane >> 2) : lane);
     const bool ok = idx < n;
     const float x = nx, y = ny, z = nz;
-    write_features<CF, GRAD, CF::P != kF32 && CF::GK == 1 && !GRAD>(myrow, ls, role, x, y, z, tfe, nd.fm);
+    if constexpr (SPLIT) st.put(lane, ls, CF::F, x, y, z);
+    else write_features<CF, GRAD, CF::P != kF32 && CF::GK == 1 && !GRAD>(myrow, ls, role, x, y, z, tfe, nd.fm);
     wave_lds_sync();
     load_pos(c + stride);
     if constexpr (ADJ) {
@@ -396,7 +463,9 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
       }
       continue;
     }
-    const f4 oo = mlp_tile<CF, GRAD>(smem, feat, nd.H, role);
+    f4 oo;
+    if constexpr (SPLIT) oo = mlp_split<CF>(smem, st, ls, nd.H);
+    else oo = mlp_tile<CF, GRAD>(smem, feat, nd.H, role);
     wave_lds_sync();
     const float o = oo[0];
     if constexpr (GRAD) {
@@ -424,14 +493,13 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
 template <class CF, int MODE, int HH = 0>
 int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, const MarchDev& m, float* out,
                     unsigned long long* stats, hipStream_t st) {
-  using G = typename CF::G;
   constexpr int TW = TileShape<MODE>::TW, TH = TileShape<MODE>::TH;
   const int tx = (vb.width + TW - 1) / TW, ty = (vb.height + TH - 1) / TH;
   const long long tiles = (long long)tx * ty * vb.n_views;
   if (tiles > 0x7fffffffLL) return kLaunchTooLarge;
   const int wpb = waves_per_block<CF, MODE>(nd.H);
   if (wpb < 1) return kLaunchNoLds;
-  const size_t shm = (size_t)fixed_lds_bytes<CF, MODE>(nd.H) + (size_t)wpb * G::FEAT_BYTES;
+  const size_t shm = (size_t)fixed_lds_bytes<CF, MODE>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, MODE>();
   // the workgroups the CUs hold at once, fewer for small launches
   const long long resident = resident_blocks<CF, MODE>(wpb, shm);
   const long long want = (tiles + wpb - 1) / wpb;
@@ -453,11 +521,10 @@ int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, cons
 template <class CF, int PM, int HH = 0>
 int launch_points_t(const NetDev& nd, const float* xyz, long long n, int key, float key_w, float* out_d,
                     float* out_g, hipStream_t st) {
-  using G = typename CF::G;
   constexpr int PER = PM == kShadeFwd ? 16 : 64;
   const int wpb = waves_per_block<CF, PM, true>(nd.H);
   if (wpb < 1) return kLaunchNoLds;
-  const size_t shm = (size_t)fixed_lds_bytes<CF, PM>(nd.H) + (size_t)wpb * G::FEAT_BYTES;
+  const size_t shm = (size_t)fixed_lds_bytes<CF, PM>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, PM, true>();
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)points_kernel<CF, PM, HH>, hipFuncAttributeMaxDynamicSharedMemorySize,
