@@ -199,9 +199,10 @@ typedef struct {
    stats (nullable, device, 3 x u64, accumulated -- the caller zeroes it):
    [0] += samples composited, [1] += rays that hit the domain, [2] += sample
    slots issued (rays per wave x march steps of the wave, idle rays included;
-   [0]/[2] is the occupancy of the matrix tiles). A wave marches 64 rays
-   without shading, 16 with forward-mode gradients and 8 with central
-   differences. Phong shading needs the density gradient, obtained as
+   [0]/[2] is the occupancy of the matrix tiles). A wave's step holds 64
+   samples without shading, 16 with forward-mode gradients and 8 with central
+   differences: one of each of as many rays, or, in launches too small to
+   fill the GPU so, 2 to 16 consecutive ones of fewer rays. Phong shading needs the density gradient, obtained as
    march->grad_mode selects (Sec. 6), for FP32, FP16 and BF16 networks
    (central differences and predicted gradients for the sine activation,
    also with a time encoding or a Fourier matrix; the adjoint for the sine

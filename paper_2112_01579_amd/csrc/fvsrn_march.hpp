@@ -65,12 +65,15 @@ constexpr int max_waves() {
   return CF::G16 ? 16 : 12;
 }
 
-// Render tile geometry per shading mode: lanes per ray and tile edges.
+// Render tile geometry per shading mode: log2 of the lanes per ray, and of the
+// tile's edges in rays when a wave takes 2^sh segments of a ray per step
+// (unshaded: 8x8 rays, then 8x4, 4x4, ...).
 template <int MODE>
 struct TileShape {
-  static constexpr int LPR = (MODE == kShadeFwd) ? 4 : (MODE == kShadeFD ? 8 : 1);
-  static constexpr int TW = LPR == 1 ? 8 : 4;
-  static constexpr int TH = 64 / LPR / TW;
+  static constexpr int LOG_LPR = (MODE == kShadeFwd) ? 2 : (MODE == kShadeFD ? 3 : 0);
+  static constexpr int LPR = 1 << LOG_LPR;
+  __host__ __device__ static constexpr int log_w(int sh) { return (7 - LOG_LPR - sh) / 2; }
+  __host__ __device__ static constexpr int log_h(int sh) { return (6 - LOG_LPR - sh) / 2; }
 };
 constexpr int kLdsBytes = 160 * 1024;
 
@@ -187,6 +190,11 @@ __device__ inline void composite(Accum& acc, const float rgba[4], float len) {
 
 // ------------------------------------------------------------- kernels
 
+// A step of a wave takes 64 samples (16 in forward mode, 8 for central
+// differences): one segment of each of its tile's rays, or,
+// with seg_shift > 0 (small launches, see segments_log2), 2^seg_shift
+// consecutive segments of fewer rays, composited by a prefix product over the
+// ray's lanes.
 // Persistent: as many workgroups as the CUs hold at once, each wave taking
 // tiles from a device-wide counter until none is left (queue[0]: the next
 // tile; queue[1]: waves done, so that the last one sets both back to zero).
@@ -196,17 +204,21 @@ __device__ inline void composite(Accum& acc, const float rgba[4], float len) {
 // wave slots on average.
 // HH: the network's layer count, compiled in for the adjoint (its saved
 // activation derivatives are registers); 0 for the other modes.
-template <class CF, int MODE, int HH = 0>
+// SEG: several segments per step (its code in the sample loop costs the
+// unshaded and forward-mode kernels 3% where it does not run; the adjoint is
+// compiled with it alone).
+template <class CF, int MODE, int HH = 0, bool SEG = MODE == kShadeAdj>
 __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(NetDev nd, TFDev tf, ViewBatch vb,
                                                                                   MarchDev m, float* out,
                                                                                   unsigned long long* stats,
                                                                                   unsigned int* queue,
-                                                                                  int tiles_x, int tiles_y) {
+                                                                                  int tiles_x, int tiles_y,
+                                                                                  int seg_shift) {
   using G = typename CF::G;
   using E = typename CF::E;
   constexpr bool GRAD = MODE == kShadeFwd;  // network run in forward (tangent) mode
   constexpr bool FD = MODE == kShadeFD;
-  constexpr int LPR = TileShape<MODE>::LPR, TW = TileShape<MODE>::TW;
+  constexpr int LPR = TileShape<MODE>::LPR;
   constexpr bool ADJ = MODE == kShadeAdj;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool SPLIT = use_split<CF, MODE>();
@@ -221,8 +233,11 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
   const int wpb = blockDim.x >> 6;
   const int tiles_per_view = tiles_x * tiles_y;
   const int n_tiles = tiles_per_view * vb.n_views;
-  const int rl = lane / LPR;  // ray within the tile
-  const int q = lane % LPR;   // role of the lane within its ray
+  const int sh = SEG ? seg_shift : 0;                // log2 of the segments a ray takes per step
+  const int q = lane % LPR;                          // role of the lane within its sample
+  const int sl = (lane / LPR) & ((1 << sh) - 1);     // the sample's segment of its ray's step
+  const int rl = (lane / LPR) >> sh;                 // ray within the tile
+  const int lw = TileShape<MODE>::log_w(sh), lh = TileShape<MODE>::log_h(sh);
   const LaneRole role = GRAD ? grad_role(q) : value_role();
   // central differences: lane q = 1..6 evaluates the sample moved by +-h along
   // axis (q-1)/2 (odd q: +h); q = 0 and 7 evaluate the sample itself
@@ -240,8 +255,8 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
   for (int tile = next_tile(queue, lane); tile < n_tiles; tile = next_tile(queue, lane)) {
     const int v = tile / tiles_per_view;
     const int tr = tile % tiles_per_view;
-    const int px = (tr % tiles_x) * TW + (rl % TW);
-    const int py = (tr / tiles_x) * TileShape<MODE>::TH + (rl / TW);
+    const int px = ((tr % tiles_x) << lw) + (rl & ((1 << lw) - 1));
+    const int py = ((tr / tiles_x) << lh) + (rl >> lw);
     const CamDev& cam = vb.cam[v];
     const LatentSrc ls = make_latent_src(nd, cam.key, cam.key_w);
     const bool in_img = px < vb.width && py < vb.height;
@@ -299,7 +314,8 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
         }
       }
     };
-    int i = 0;
+    int i = sl;  // this lane's next segment of its ray
+    active = active && (sh == 0 || i < ray.nseg);
     while (__builtin_amdgcn_ballot_w64(active)) {
       ++iters;
       float len, sx, sy, sz;
@@ -367,16 +383,44 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
           phong(rgba, gx, gy, gz, ray.d, m);
         }
       }
-      composite(acc, rgba, comp ? len : 0.0f);
-      i += comp ? 1 : 0;
-      active = comp && !(acc.T < m.ert_eps) && i < ray.nseg;
+      if (sh == 0) {
+        composite(acc, rgba, comp ? len : 0.0f);
+        i += comp ? 1 : 0;
+        active = comp && !(acc.T < m.ert_eps) && i < ray.nseg;
+      } else {
+        // the ray's 2^sh segments front to back: each lane's transmittance
+        // from the product of those before it, its colour into the lane's
+        // own sum; a segment behind the one that ends the ray is left out
+        const float trn = fast_exp(-rgba[3] * (comp ? len : 0.0f));
+        float inc = trn;
+        for (int d = 1; d < (1 << sh); d <<= 1) {
+          const float up = __shfl_up(inc, d * LPR, 64);
+          inc *= sl >= d ? up : 1.0f;
+        }
+        const float before = __shfl_up(inc, LPR, 64), last = __shfl(inc, lane | (((1 << sh) - 1) * LPR), 64);
+        const float T = sl ? acc.T * before : acc.T;
+        const bool in = comp && !(sl && T < m.ert_eps);
+        const float ta = in ? T * (1.0f - trn) : 0.0f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) acc.C[a] = fmaf(ta, rgba[a], acc.C[a]);
+        acc.A += ta;
+        acc.T *= last;
+        n_samp += in && q == 0 ? 1ull : 0ull;
+        i += 1 << sh;
+        active = active && !(acc.T < m.ert_eps) && i < ray.nseg;
+      }
     }
-    const bool owner = q == 0;
+    for (int d = 1; d < (1 << sh); d <<= 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) acc.C[a] += __shfl_xor(acc.C[a], d * LPR, 64);
+      acc.A += __shfl_xor(acc.A, d * LPR, 64);
+    }
+    const bool owner = q == 0 && sl == 0;
     if (in_img && owner) {
       float4* o = reinterpret_cast<float4*>(out) + ((long long)v * vb.height + py) * vb.width + px;
       *o = make_float4(acc.C[0], acc.C[1], acc.C[2], acc.A);
     }
-    n_samp += owner ? (unsigned long long)i : 0ull;
+    if (sh == 0) n_samp += owner ? (unsigned long long)i : 0ull;
     n_hit += (owner && in_img && ray.hit && ray.nseg > 0) ? 1ull : 0ull;
   }
   if (stats) {
@@ -490,31 +534,66 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
 
 // ------------------------------------------------------------ launchers
 
+// log2 of the consecutive segments of a ray that one step of a wave takes
+// (see march_kernel), for `slots` waves resident on the GPU. Tiles of one
+// segment per ray leave a small launch with idle waves and serial rays, and
+// a middle-sized one with few tiles per wave and a long tail, so a ray takes
+// more segments until there are 32 tiles per wave slot: up to 16 while the
+// one-segment tiles are under 4 per slot, else up to 4, since a ray that ends
+// early leaves the rest of its step unused; and never so many that a chord
+// has under 4 steps. Measured, one segment against the rule's, ms per launch:
+// 64^2 x 128 steps FP32 0.561 -> 0.078 (16); FP16 study network 256^2 3.19 ->
+// 0.61 (16), 512^2 3.34 -> 2.01 (16; 8: 1.99), 1024^2 8.50 -> 7.43 (4), 8 x
+// 1024^2 52.2 -> 52.2 (1; 4: 52.3, 16: 54.9); 1920x1080 c = 48 adjoint 48.1 ->
+// 44.9 (4; 8: 44.6).
+template <int MODE>
+int segments_log2(const ViewBatch& vb, const MarchDev& m, long long slots) {
+  const int lw = TileShape<MODE>::log_w(0), lh = TileShape<MODE>::log_h(0);
+  const long long tiles =
+      (long long)((vb.width + (1 << lw) - 1) >> lw) * ((vb.height + (1 << lh) - 1) >> lh) * vb.n_views;
+  const double chord = m.fixed_steps > 0 ? m.fixed_steps : 3.4641016 / m.step;  // segments of the longest
+  const int most = tiles >= 4 * slots ? 2 : (lw + lh < 4 ? lw + lh : 4);
+  int sh = 0;
+  while (sh < most && (tiles << sh) < 32 * slots && (double)(8 << sh) <= chord) ++sh;
+  return sh;
+}
+
+template <class CF, int MODE, int HH, bool SEG>
+void launch_march(long long blocks, int wpb, size_t shm, const NetDev& nd, const TFDev& tf, const ViewBatch& vb,
+                  const MarchDev& m, float* out, unsigned long long* stats, unsigned int* queue, int tx, int ty, int sh,
+                  hipStream_t st) {
+  static bool attr = false;
+  if (!attr) {
+    (void)hipFuncSetAttribute((const void*)march_kernel<CF, MODE, HH, SEG>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    attr = true;
+  }
+  hipLaunchKernelGGL((march_kernel<CF, MODE, HH, SEG>), dim3((unsigned)blocks), dim3(wpb * 64), shm, st, nd, tf, vb, m,
+                     out, stats, queue, tx, ty, sh);
+}
+
 template <class CF, int MODE, int HH = 0>
 int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, const MarchDev& m, float* out,
                     unsigned long long* stats, hipStream_t st) {
-  constexpr int TW = TileShape<MODE>::TW, TH = TileShape<MODE>::TH;
-  const int tx = (vb.width + TW - 1) / TW, ty = (vb.height + TH - 1) / TH;
-  const long long tiles = (long long)tx * ty * vb.n_views;
-  if (tiles > 0x7fffffffLL) return kLaunchTooLarge;
   const int wpb = waves_per_block<CF, MODE>(nd.H);
   if (wpb < 1) return kLaunchNoLds;
   const size_t shm = (size_t)fixed_lds_bytes<CF, MODE>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, MODE>();
   // the workgroups the CUs hold at once, fewer for small launches
   const long long resident = resident_blocks<CF, MODE>(wpb, shm);
+  const int sh = segments_log2<MODE>(vb, m, resident * wpb);
+  const int tw = 1 << TileShape<MODE>::log_w(sh), th = 1 << TileShape<MODE>::log_h(sh);
+  const int tx = (vb.width + tw - 1) / tw, ty = (vb.height + th - 1) / th;
+  const long long tiles = (long long)tx * ty * vb.n_views;
+  if (tiles > 0x7fffffffLL) return kLaunchTooLarge;
   const long long want = (tiles + wpb - 1) / wpb;
   const long long blocks = want < resident ? want : resident;
   if (blocks < 1) return 0;
   unsigned int* queue = tile_queue_slot();
   if (!queue) return 2;
-  static bool attr = false;
-  if (!attr) {
-    (void)hipFuncSetAttribute((const void*)march_kernel<CF, MODE, HH>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kLdsBytes);
-    attr = true;
-  }
-  hipLaunchKernelGGL((march_kernel<CF, MODE, HH>), dim3((unsigned)blocks), dim3(wpb * 64), shm, st, nd, tf, vb, m,
-                     out, stats, queue, tx, ty);
+  if (sh > 0 || MODE == kShadeAdj)
+    launch_march<CF, MODE, HH, true>(blocks, wpb, shm, nd, tf, vb, m, out, stats, queue, tx, ty, sh, st);
+  else
+    launch_march<CF, MODE, HH, MODE == kShadeAdj>(blocks, wpb, shm, nd, tf, vb, m, out, stats, queue, tx, ty, 0, st);
   return check_launch();
 }
 
