@@ -51,71 +51,200 @@ __device__ inline float dense_sample(const float* vol, int nx, int ny, int nz, f
 
 constexpr int kDenseThreads = 256;
 
-__global__ __launch_bounds__(kDenseThreads) void dense_march_kernel(const float* vol, int nx, int ny,
-                                                                    int nz, TFDev tf, ViewBatch vb,
-                                                                    MarchDev m, float* out,
-                                                                    unsigned long long* stats,
-                                                                    int tiles_x, int tiles_y) {
+// Tile of a wave of the dense march: a step takes S = 2^ls consecutive
+// segments of R = 128 / S rays (ls >= 1), in two passes over G = 64 / S rays
+// each. Rays are numbered pass by pass, row by row within a pass's block; the
+// second pass's block lies below the first's.
+struct DenseTile {
+  int ls;
+  __host__ __device__ int rays() const { return 128 >> ls; }
+  __host__ __device__ int lw() const { return (7 - ls) / 2; }  // log2 of the tile's edges
+  __host__ __device__ int lh() const { return (6 - ls) / 2 + 1; }
+  __device__ int x(int r) const { return r & ((1 << lw()) - 1); }
+  __device__ int y(int r) const { return r >> lw(); }
+};
+
+// Dense DVR. The volume is read through L1 lookups, one per 128-byte line that
+// a group of four lanes touches, and with one segment of 8x8 rays per wave
+// these bound the march (27 per load of 64 lanes, one per CU and cycle). A
+// wave therefore takes four segments of 4x4 rays per load: its lanes are as
+// close in depth as they are across, and the lanes of a group are kept
+// together along x, the volume's contiguous axis -- neighbouring pixels, or,
+// where the view looks along x (the forward direction's x beyond 0.6), two
+// segments of one ray. Each lane takes its samples through the transfer
+// function and leaves colour and transmittance in LDS, from where the ray's
+// own lane composites them in order: the image is the same, bit for bit,
+// whatever the tile. A step has two passes, which hide each other's loads (one
+// pass: 11.3 ms for 8 x 1024^2, four: 9.9). 256^3 volume, 1024^2 views, before
+// and now: along z 1.22 -> 1.22 ms, 22 degrees off 1.47 -> 1.27, 45 1.66 -> 1.46,
+// 67 1.72 -> 1.36, along x 1.64 -> 1.25, an orbit of eight 10.3 -> 9.1 (the VALU
+// and the lookups are then about even); small launches: launch_render_dense.
+template <bool PHONG, bool BIG>
+__global__ __launch_bounds__(kDenseThreads, PHONG ? 4 : 5) void dense_march_kernel(const float* vol, int nx, int ny, int nz, TFDev tf,
+                                                                    ViewBatch vb, MarchDev m, float* out,
+                                                                    unsigned long long* stats, int tiles_x,
+                                                                    int tiles_y, DenseTile dt) {
+  constexpr int Q = 2;
+  __shared__ f4 rays[kDenseThreads / 64][3][64];
+  __shared__ f4 samples[kDenseThreads / 64][128];  // [segment][ray]: colour, transmittance (< 0: none)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int tiles_per_view = tiles_x * tiles_y;
-  const int tile = xcd_block_d(gridDim.x) * (kDenseThreads / 64) + wave;
+  const int tile = __builtin_amdgcn_readfirstlane(xcd_block_d(gridDim.x) * (kDenseThreads / 64) + wave);
   if (tile >= tiles_per_view * vb.n_views) return;
-  const int v = tile / tiles_per_view;
-  const int tr = tile % tiles_per_view;
-  const int px = (tr % tiles_x) * 8 + (lane & 7);
-  const int py = (tr / tiles_x) * 8 + (lane >> 3);
-  if (px >= vb.width || py >= vb.height) return;
-  const CamDev& cam = vb.cam[v];
-  Ray ray = make_ray(cam, px, py, vb.width, vb.height, m);
-  const bool fixed = m.fixed_steps > 0;
-  float T = 1.0f, Cr = 0.0f, Cg = 0.0f, Cb = 0.0f, A = 0.0f;
-  int i = 0;
-  const float hx = 2.0f / (float)(nx - 1), hy = 2.0f / (float)(ny - 1), hz = 2.0f / (float)(nz - 1);
-  for (; i < ray.nseg; ++i) {
-    const float a0 = ray.t0 + (float)i * ray.ds;
-    float a1 = ray.t0 + (float)(i + 1) * ray.ds;
-    if (!fixed) a1 = fminf(a1, ray.t1);
-    const float len = a1 - a0, tm = 0.5f * (a0 + a1);
-    if (len <= 0.0f) break;
-    const float sx = ray.o[0] + tm * ray.d[0];
-    const float sy = ray.o[1] + tm * ray.d[1];
-    const float sz = ray.o[2] + tm * ray.d[2];
-    const float d = dense_sample(vol, nx, ny, nz, sx, sy, sz);
-    float rgba[4];
-    tf_eval_d(tf, d, rgba);
-    if (m.phong) {
-      const float gx = (dense_sample(vol, nx, ny, nz, sx + hx, sy, sz) -
-                        dense_sample(vol, nx, ny, nz, sx - hx, sy, sz)) / (2.0f * hx);
-      const float gy = (dense_sample(vol, nx, ny, nz, sx, sy + hy, sz) -
-                        dense_sample(vol, nx, ny, nz, sx, sy - hy, sz)) / (2.0f * hy);
-      const float gz = (dense_sample(vol, nx, ny, nz, sx, sy, sz + hz) -
-                        dense_sample(vol, nx, ny, nz, sx, sy, sz - hz)) / (2.0f * hz);
-      const float gl = sqrtf(gx * gx + gy * gy + gz * gz);
-      if (gl >= 1e-6f) {
-        const float ndl = fabsf(gx * ray.d[0] + gy * ray.d[1] + gz * ray.d[2]) / gl;
-        const float spec = m.ks * powf(ndl, m.shininess);
-        const float k = m.ka + m.kd * ndl;
-        rgba[0] = rgba[0] * k + spec;
-        rgba[1] = rgba[1] * k + spec;
-        rgba[2] = rgba[2] * k + spec;
+  const int S = 1 << dt.ls, R = dt.rays(), G = 64 >> dt.ls;
+  f4(*rw)[64] = rays[wave];
+  f4* sw = samples[wave];
+  __amdgpu_buffer_rsrc_t rsrc;
+  if constexpr (!BIG) rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vol), 0, nx * ny * nz * 4, 0x00020000);
+  // the rows along x of the cell around p, and p's fractions in it
+  auto cell_rows = [&](const float p[3], f2 row[4], float f[3]) {
+    int c[3];
+    axis_cell(p[0], nx, c[0], f[0]);
+    axis_cell(p[1], ny, c[1], f[1]);
+    axis_cell(p[2], nz, c[2], f[2]);
+    if constexpr (BIG) {
+      const float* b = vol + ((long long)c[2] * ny + c[1]) * nx + c[0];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float* e = b + (k & 1 ? nx : 0) + (k >> 1 ? (long long)nx * ny : 0);
+        row[k] = f2{e[0], e[1]};
       }
+    } else {
+      const unsigned at = ((unsigned)(c[2] * ny + c[1]) * (unsigned)nx + (unsigned)c[0]) * 4u;
+      const unsigned sy = (unsigned)nx * 4u, sz = (unsigned)ny * sy;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        row[k] = __builtin_bit_cast(
+            f2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (k & 1 ? sy : 0u) + (k >> 1 ? sz : 0u), 0));
     }
-    const float trn = fast_exp(-rgba[3] * len);
-    const float ta = T * (1.0f - trn);
-    Cr = fmaf(ta, rgba[0], Cr);
-    Cg = fmaf(ta, rgba[1], Cg);
-    Cb = fmaf(ta, rgba[2], Cb);
-    A += ta;
-    T *= trn;
-    if (T < m.ert_eps) { ++i; break; }
+  };
+  auto trilinear = [](const f2 row[4], const float f[3]) {
+    const float c00 = row[0][0] + f[0] * (row[0][1] - row[0][0]);
+    const float c10 = row[1][0] + f[0] * (row[1][1] - row[1][0]);
+    const float c01 = row[2][0] + f[0] * (row[2][1] - row[2][0]);
+    const float c11 = row[3][0] + f[0] * (row[3][1] - row[3][0]);
+    const float c0 = c00 + f[1] * (c10 - c00);
+    const float c1 = c01 + f[1] * (c11 - c01);
+    return c0 + f[2] * (c1 - c0);
+  };
+  auto sample = [&](float x, float y, float z) {
+    const float p[3] = {x, y, z};
+    f2 row[4];
+    float f[3];
+    cell_rows(p, row, f);
+    return trilinear(row, f);
+  };
+  const bool fixed = m.fixed_steps > 0;
+  const float hx = 2.0f / (float)(nx - 1), hy = 2.0f / (float)(ny - 1), hz = 2.0f / (float)(nz - 1);
+  const int v = tile / tiles_per_view, tr = tile % tiles_per_view;
+  const CamDev& cam = vb.cam[v];
+  // a lane's ray within the pass and its segment: segment bits at either end of the lane index
+  const int low = dt.ls > 0 && fabs(cam.fwd[0]) > 0.6 ? 1 : 0;
+  const int rl = (lane >> low) & (G - 1), sl = (lane & ((1 << low) - 1)) | (lane >> (6 - dt.ls + low) << low);
+  const int px = ((tr % tiles_x) << dt.lw()) + dt.x(lane), py = ((tr / tiles_x) << dt.lh()) + dt.y(lane);
+  const bool owner = lane < R && px < vb.width && py < vb.height;
+  int nseg = 0;
+  if (lane < R) {
+    const Ray r = make_ray(cam, owner ? px : 0, owner ? py : 0, vb.width, vb.height, m);
+    nseg = owner && r.hit ? r.nseg : 0;
+    rw[0][lane] = f4{r.o[0], r.o[1], r.o[2], r.t0};
+    rw[1][lane] = f4{r.d[0], r.d[1], r.d[2], r.ds};
+    rw[2][lane] = f4{r.t1, __int_as_float(nseg), 0.0f, 0.0f};
   }
-  float4* o = reinterpret_cast<float4*>(out) + ((long long)v * vb.height + py) * vb.width + px;
-  *o = make_float4(Cr, Cg, Cb, A);
+  float T = 1.0f, Cr = 0.0f, Cg = 0.0f, Cb = 0.0f, A = 0.0f;
+  int n = 0;
+  bool active = nseg > 0;
+  for (int i0 = 0;; i0 += S) {
+    if (!__builtin_amdgcn_ballot_w64(active)) break;
+    wave_lds_sync();
+    const int i = i0 + sl;
+    float len[Q], d[Q], px3[Q][3];
+    bool has[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int r = q * G + rl;
+      const f4 ro = rw[0][r], rd = rw[1][r], re = rw[2][r];
+      const float a0 = ro[3] + (float)i * rd[3];
+      float a1 = ro[3] + (float)(i + 1) * rd[3];
+      if (!fixed) a1 = fminf(a1, re[0]);
+      const float tm = 0.5f * (a0 + a1);
+      len[q] = a1 - a0;
+      has[q] = i < __float_as_int(re[1]) && len[q] > 0.0f;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) px3[q][a] = ro[a] + tm * rd[a];
+    }
+    f2 rows[Q][4];
+    float fr[Q][3];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (has[q]) cell_rows(px3[q], rows[q], fr[q]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) d[q] = has[q] ? trilinear(rows[q], fr[q]) : 0.0f;
+    float rgba[Q][4];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) rgba[q][c] = tf.base[c];
+    for (int j = 0; j < tf.n_seg; ++j)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const float w = __builtin_amdgcn_fmed3f(fmaf(d[q], tf.inv[j], tf.off[j]), 0.0f, 1.0f);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) rgba[q][c] = fmaf(w, tf.delta[j][c], rgba[q][c]);
+      }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int r = q * G + rl;
+      if constexpr (PHONG) {
+        if (has[q]) {
+          const float sx = px3[q][0], sy = px3[q][1], sz = px3[q][2];
+          const float gx = (sample(sx + hx, sy, sz) - sample(sx - hx, sy, sz)) / (2.0f * hx);
+          const float gy = (sample(sx, sy + hy, sz) - sample(sx, sy - hy, sz)) / (2.0f * hy);
+          const float gz = (sample(sx, sy, sz + hz) - sample(sx, sy, sz - hz)) / (2.0f * hz);
+          const float gl = sqrtf(gx * gx + gy * gy + gz * gz);
+          if (gl >= 1e-6f) {
+            const f4 r1 = rw[1][r];
+            const float ndl = fabsf(gx * r1[0] + gy * r1[1] + gz * r1[2]) / gl;
+            const float spec = m.ks * powf(ndl, m.shininess);
+            const float k = m.ka + m.kd * ndl;
+            rgba[q][0] = rgba[q][0] * k + spec;
+            rgba[q][1] = rgba[q][1] * k + spec;
+            rgba[q][2] = rgba[q][2] * k + spec;
+          }
+        }
+      }
+      sw[sl * R + r] = f4{rgba[q][0], rgba[q][1], rgba[q][2], has[q] ? fast_exp(-rgba[q][3] * len[q]) : -1.0f};
+    }
+    wave_lds_sync();
+    for (int k = 0; k < S; ++k) {
+      const f4 e = sw[k * R + (lane & (R - 1))];
+      active = active && e[3] >= 0.0f;
+      const float trn = active ? e[3] : 1.0f;
+      const float ta = T * (1.0f - trn);
+      Cr = fmaf(ta, e[0], Cr);
+      Cg = fmaf(ta, e[1], Cg);
+      Cb = fmaf(ta, e[2], Cb);
+      A += ta;
+      T *= trn;
+      n += active ? 1 : 0;
+      active = active && !(T < m.ert_eps);
+    }
+    active = active && i0 + S < nseg;
+    if (lane < R && !active) rw[2][lane][1] = __int_as_float(0);  // an ended ray takes no more samples
+  }
+  if (owner)
+    reinterpret_cast<float4*>(out)[((long long)v * vb.height + py) * vb.width + px] = make_float4(Cr, Cg, Cb, A);
   if (stats) {
-    unsigned long long mine = (unsigned long long)i, hit = (ray.hit && ray.nseg > 0) ? 1ull : 0ull;
-    atomicAdd(stats, mine);
-    atomicAdd(stats + 2, mine);
-    if (hit) atomicAdd(stats + 1, 1ull);
+    unsigned mine = (unsigned)n, hit = nseg > 0 ? 1u : 0u;
+    for (int off = 32; off > 0; off >>= 1) {
+      mine += (unsigned)__shfl_xor((int)mine, off, 64);
+      hit += (unsigned)__shfl_xor((int)hit, off, 64);
+    }
+    if (lane == 0) {
+      atomicAdd(stats, (unsigned long long)mine);
+      atomicAdd(stats + 1, (unsigned long long)hit);
+      atomicAdd(stats + 2, (unsigned long long)mine);
+    }
   }
 }
 
@@ -605,12 +734,36 @@ int launch_points(const NetDev& net, int prec, const float* xyz, long long n, in
 
 int launch_render_dense(const float* vol, int nx, int ny, int nz, const TFDev& tf, const ViewBatch& vb,
                         const MarchDev& m, float* out, unsigned long long* stats, void* stream) {
-  const int tx = (vb.width + 7) / 8, ty = (vb.height + 7) / 8;
+  // Segments per step and ray: 4 while that gives 48 tiles per CU, more in
+  // smaller launches, whose rays would leave the GPU idle (ms at 4 / 8 / 16 /
+  // 64 segments: two 800 x 600 views 1.20 / 1.18 / 1.38 / 3.39, one of 512^2
+  // 0.59 / 0.54 / 0.54 / 1.21, 200 x 150 0.24 / 0.15 / 0.11 / 0.16, 40 x 40
+  // 0.27 / 0.16 / 0.10 / 0.06; before 1.31, 1.03, 0.45 and 0.60). Phong starts at
+  // 8 (two 800 x 600 views 7.8 / 7.5 / 7.7, before 9.4): its seven samples keep
+  // the lanes' loads in flight.
+  DenseTile dt = {m.phong ? 3 : 2};
+  const double chord = m.fixed_steps > 0 ? m.fixed_steps : 3.4641016 / m.step;
+  auto tiles_at = [&](int ls) {
+    const DenseTile t = {ls};
+    const long long tw = 1 << t.lw(), th = 1 << t.lh();
+    return ((vb.width + tw - 1) / tw) * ((vb.height + th - 1) / th) * vb.n_views;
+  };
+  while (dt.ls < 6 && tiles_at(dt.ls) < device_cus() * (dt.ls == 2 ? 48ll : (dt.ls == 3 ? 12ll : 4ll)) &&
+         (double)(4 << dt.ls) <= chord)
+    ++dt.ls;
+  if (tiles_at(dt.ls) > 1ll << 25) dt.ls = 1;  // tiles of 64 rays near the grid's limit
+  const int tw = 1 << dt.lw(), th = 1 << dt.lh();
+  const int tx = (vb.width + tw - 1) / tw, ty = (vb.height + th - 1) / th;
   const long long tiles = (long long)tx * ty * vb.n_views;
   long long blocks = (tiles + 3) / 4;
   if (blocks % 8) blocks += 8 - blocks % 8;
-  hipLaunchKernelGGL(dense_march_kernel, dim3((unsigned)blocks), dim3(kDenseThreads), 0, (hipStream_t)stream,
-                     vol, nx, ny, nz, tf, vb, m, out, stats, tx, ty);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kDenseThreads), 0, (hipStream_t)stream, vol, nx, ny, nz, tf,
+                       vb, m, out, stats, tx, ty, dt);
+  };
+  const bool big = (long long)nx * ny * nz >= (1ll << 29);  // 2^31 bytes
+  if (m.phong) big ? go(dense_march_kernel<true, true>) : go(dense_march_kernel<true, false>);
+  else big ? go(dense_march_kernel<false, true>) : go(dense_march_kernel<false, false>);
   return check_launch();
 }
 

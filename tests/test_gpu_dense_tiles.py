@@ -1,0 +1,102 @@
+"""Dense DVR at every tile of its launch rule (4 to 64 segments of a ray per
+step, by the size of the launch and the chord's length): images and sample
+counts against the FP64 oracle, and the same image bit for bit whichever tile
+a view is rendered with."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2112_01579_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5  # FP32 against the FP64 oracle
+PHONG_TOL = 1e-4
+
+
+@pytest.fixture(scope="module")
+def FV():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2112_01579_amd import fvsrn
+    fvsrn.lib()
+    return fvsrn
+
+
+def _vol():
+    v = I.gaussian_volume(48, 24, 7)
+    return np.ascontiguousarray(v[:41, :, :45])  # nz, ny, nx = 41, 48, 45
+
+
+def _cam(axis, w, h):
+    eye = {"x": (2.9, 0.3, 0.2), "y": (0.2, 2.9, 0.3), "z": (0.3, 0.2, 2.9), "xz": (2.0, 0.4, 2.1),
+           "in": (0.1, -0.2, 0.3)}[axis]
+    return I.Camera(ortho=False, eye=eye, target=(0.0, 0.0, -0.5 if axis == "in" else 0.0),
+                    up=(0.0, 0.0, 1.0) if axis == "y" else (0.0, 1.0, 0.0), width=w, height=h, fov_y_deg=48.0)
+
+
+def _render(FV, vol, cams, m):
+    stats = torch.zeros(3, dtype=torch.int64, device="cuda")
+    img = FV.fvsrn_render_dense(torch.from_numpy(vol).cuda(), I.ramp_tf(), cams, m, stats=stats).cpu().numpy()
+    return img, stats.cpu().numpy()
+
+
+@pytest.mark.parametrize("axis", ["x", "y", "z", "xz", "in"])
+@pytest.mark.parametrize("per_unit", [1, 3, 6, 12, 40])
+def test_dense_small(FV, axis, per_unit):
+    """Small launches: the chord's length limits the segments (longest 3.5,
+    10, 21, 42 and 139: 4, 8, 16, 32 and 64 of them)."""
+    vol, cam, m = _vol(), _cam(axis, 39, 23), I.March(step=1.0 / per_unit)
+    img, stats = _render(FV, vol, [cam], m)
+    ref, ns = O.render(O.Field(vol=vol), I.ramp_tf(), [cam], m)
+    err = float(np.abs(img - ref).max())
+    print("dense %s 1/%d err %.3g" % (axis, per_unit, err), flush=True)
+    assert err <= TOL and stats[0] == ns and stats[2] == ns
+
+
+@pytest.mark.parametrize("fixed", [1, 2, 5, 64, 65])
+def test_dense_fixed_steps(FV, fixed):
+    vol, m = _vol(), I.March(step=0.0, fixed_steps=fixed)
+    cams = [I.ortho_camera(21, 34)]
+    img, stats = _render(FV, vol, cams, m)
+    ref, ns = O.render(O.Field(vol=vol), I.ramp_tf(), cams, m)
+    assert float(np.abs(img - ref).max()) <= TOL and stats[0] == ns
+
+
+@pytest.mark.parametrize("eps", [0.05, 0.5])
+@pytest.mark.parametrize("axis", ["x", "z"])
+def test_dense_termination(FV, axis, eps):
+    vol, cam = _vol(), _cam(axis, 39, 23)
+    img, stats = _render(FV, vol, [cam], I.March(step=1.0 / 40, ert_eps=eps))
+    refs = [O.render(O.Field(vol=vol), I.ramp_tf(), [cam], I.March(step=1.0 / 40, ert_eps=e))
+            for e in (eps, eps * (1 - 1e-4), eps * (1 + 1e-4))]
+    assert float(np.min([np.abs(img - r).max(-1) for r, _ in refs], axis=0).max()) <= TOL
+    counts = [n for _, n in refs]
+    assert min(counts) <= stats[0] <= max(counts)
+
+
+@pytest.mark.parametrize("phong", [False, True])
+def test_dense_same_image_in_every_launch(FV, phong):
+    """One view alone, among 16 of its kind and in a large image of 16 views of
+    larger size: tiles of 64 down to 4 segments (8 for Phong), one result."""
+    vol = _vol()
+    m = I.March(step=1.0 / 40, ert_eps=1e-3, phong=phong)
+    for w, h, copies in ((40, 30, (1, 5, 16)), (200, 150, (1, 4, 16)), (480, 360, (1, 3, 16))):
+        cams = [_cam(a, w, h) for a in ("x", "z", "xz", "in")]
+        first = None
+        for k in copies:
+            img, _ = _render(FV, vol, (cams * 4)[:max(4, k)] if k > 1 else cams, m)
+            one = np.stack([_render(FV, vol, [c], m)[0][0] for c in cams]) if k == 1 else img[:4]
+            first = one if first is None else first
+            assert np.array_equal(first, one)
+
+
+def test_dense_phong_small(FV):
+    vol, cam = _vol(), _cam("xz", 39, 23)
+    m = I.March(step=1.0 / 40, phong=True)
+    img, stats = _render(FV, vol, [cam], m)
+    ref, ns = O.render(O.Field(vol=vol), I.ramp_tf(), [cam], m)
+    err = float(np.abs(img - ref).max())
+    print("dense phong err %.3g" % err, flush=True)
+    assert err <= PHONG_TOL and stats[0] == ns
