@@ -1,7 +1,7 @@
 """Dense DVR at every tile of its launch rule (4 to 64 segments of a ray per
 step, by the size of the launch and the chord's length): images and sample
 counts against the FP64 oracle, and the same image bit for bit whichever tile
-a view is rendered with."""
+a view is rendered with. SSIM at the edges of its tiles."""
 import numpy as np
 import pytest
 import torch
@@ -100,3 +100,15 @@ def test_dense_phong_small(FV):
     err = float(np.abs(img - ref).max())
     print("dense phong err %.3g" % err, flush=True)
     assert err <= PHONG_TOL and stats[0] == ns
+
+
+@pytest.mark.parametrize("w,h", [(11, 11), (74, 26), (75, 27), (73, 25), (138, 11), (11, 42)])
+def test_ssim_tile_edges(FV, w, h):
+    """Output sizes around one tile of 64 x 16 (1 x 1, exactly one, one more and one fewer each way)."""
+    rng = np.random.default_rng(w * 100 + h)
+    a = rng.uniform(size=(2, h, w, 4)).astype(np.float32)
+    b = (a + rng.normal(0.0, 0.1, a.shape)).astype(np.float32)
+    got = FV.fvsrn_ssim_map(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()).cpu().numpy()
+    for i in range(2):
+        _, ref = O.ssim(a[i], b[i], with_map=True)
+        assert got[i].shape == ref.shape and float(np.abs(got[i] - ref).max()) <= 1e-5
