@@ -5,7 +5,7 @@
 //
 // fwd_bwd_kernel: each wave takes chunks of S = 16 points (fixed,
 // grid-independent assignment: chunk c goes to wave c mod n_waves; one MFMA
-// N-tile per chunk keeps the per-wave LDS small enough for six waves per CU).
+// N-tile per chunk keeps the per-wave LDS small enough for eight waves per CU).
 // Per chunk:
 //   1. the wave's 64 lanes write the chunk's 16 input rows to LDS, four lanes
 //      per point (write_row_quad);
@@ -59,13 +59,18 @@ struct TrainCfg {
   static constexpr int ZS = 20;                     // latent-gradient row stride
   // per-wave LDS (bytes)
   static constexpr int FEAT = S * G::ROW * 4;
+  // Pre-activations a_i, each replaced by delta_i once the backward pass has
+  // read it (its sine was last needed by layer i + 1); dL/dz takes the place of
+  // the input rows, which layer 0's weight gradient reads last. With buffers
+  // of their own a wave needed 17.8 KB and six fitted a CU (c = 32, H = 4), so
+  // that 2048 waves ran in two rounds; 14.2 KB fit eight and one round
+  // (2^18-point Adam step of the study network 326 -> 213 us).
   __host__ __device__ static int abuf_bytes(int H) { return H * S * AS * 4; }
-  static constexpr int DBUF = S * AS * 4;
   static constexpr int DY = 64 * 4;                 // dL/dy [output][sample]
   static_assert(4 * S <= 64, "four outputs of S samples must fit the dL/dy buffer");
-  static constexpr int ZBUF = S * ZS * 4;
+  static_assert(S * ZS * 4 <= FEAT, "dL/dz must fit the input rows");
   static constexpr int BACC = MT * 4 * 16;          // one layer's bias sums: [M-tile][row group] f4
-  __host__ __device__ static int wave_bytes(int H) { return FEAT + abuf_bytes(H) + DBUF + DY + ZBUF + (H - 1) * BACC; }
+  __host__ __device__ static int wave_bytes(int H) { return FEAT + abuf_bytes(H) + DY + (H - 1) * BACC; }
   // The backward pass needs W^T. For c = 32 a transposed copy of each hidden
   // layer and of W_0's latent columns is staged once per workgroup (14 KiB at
   // H = 4: one wave of seven fewer per CU, but lane-contiguous reads); wider
@@ -272,12 +277,11 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
   char* wbase = back + TC::back_bytes(H) + wave_l * TC::wave_bytes(H);
   float* feat = reinterpret_cast<float*>(wbase);
   float* abuf = reinterpret_cast<float*>(wbase + TC::FEAT);
-  float* dbuf = reinterpret_cast<float*>(wbase + TC::FEAT + TC::abuf_bytes(H));
-  float* dy = reinterpret_cast<float*>(wbase + TC::FEAT + TC::abuf_bytes(H) + TC::DBUF);
-  float* zbuf = reinterpret_cast<float*>(wbase + TC::FEAT + TC::abuf_bytes(H) + TC::DBUF + TC::DY);
+  float* dy = reinterpret_cast<float*>(wbase + TC::FEAT + TC::abuf_bytes(H));
+  float* zbuf = feat;  // dL/dz, over the input rows
   // bias gradients of the hidden layers, summed over the chunk's points in the
   // wave and accumulated here over its chunks ([layer][M-tile][row group])
-  f4* bacc = reinterpret_cast<f4*>(wbase + TC::FEAT + TC::abuf_bytes(H) + TC::DBUF + TC::DY + TC::ZBUF);
+  f4* bacc = reinterpret_cast<f4*>(wbase + TC::FEAT + TC::abuf_bytes(H) + TC::DY);
   for (int e = lane; e < (H - 1) * MT * 4; e += kWave) bacc[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   float* slice = ws + (size_t)wave * TC::slice(H);
   const float* W0 = reinterpret_cast<const float*>(smem);
@@ -488,6 +492,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
         }
       }
     }
+    wave_lds_sync();  // the sums above read a_{H-1}, which delta_{H-1} replaces
     for (int i = H - 1; i >= 0; --i) {
       constexpr int NW = MT * (TC::NK0 > MT ? TC::NK0 : MT);
       f4 oldw[NW];
@@ -496,7 +501,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
       } else {
         if (!kResident0 || i != H - 1) load_tiles(TC::tile_h(H, i, 0, 0), MT * MT, oldw);
       }
-      const float* ai = abuf + i * S * AS;
+      float* ai = abuf + i * S * AS;  // a_i, then delta_i in its place
       // delta_i = d L / d x_i = (d L / d h_i) * act'(x_i), x = W h + b in
       // world units (a_i holds x / (2 pi) for the periodic activations)
       f4 dbias[MT];
@@ -511,7 +516,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
 #pragma unroll
           for (int j = 0; j < 4; ++j) da[j] = dh[t][mt][j] * act_d<ACT>(a[j]);
           dh[t][mt] = da;
-          *reinterpret_cast<f4*>(dbuf + (16 * t + nn) * AS + 16 * mt + 4 * g) = da;
+          *reinterpret_cast<f4*>(ai + (16 * t + nn) * AS + 16 * mt + 4 * g) = da;
           dbias[mt] += da;
         }
       if (i >= 1) {
@@ -534,7 +539,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
 #pragma unroll
             for (int q = 0; q < S / 4; ++q) {
               const int s = 4 * q + g;
-              const float a = dbuf[s * AS + 16 * mo + nn];
+              const float a = ai[s * AS + 16 * mo + nn];
               const float b = col < G::KROW ? feat[s * G::ROW + col] : 0.0f;
               dw = PR::mma(a, b, dw);
             }
@@ -554,7 +559,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
 #pragma unroll
             for (int q = 0; q < S / 4; ++q) {
               const int s = 4 * q + g;
-              const float a = dbuf[s * AS + 16 * mo + nn];
+              const float a = ai[s * AS + 16 * mo + nn];
               const float b = act_el<ACT, false>(ap[s * AS + 16 * nk + nn], value_role());
               dw = PR::mma(a, b, dw);
             }
@@ -592,6 +597,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
         }
       } else {
         // d L / d z = W_0[:, latent]^T delta_0 -> zbuf[s][f]
+        wave_lds_sync();
 #pragma unroll
         for (int t = 0; t < NTC; ++t) {
           f4 dz = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -626,6 +632,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
         dst[q] = make_float4(zbuf[lane * TC::ZS + 4 * q], zbuf[lane * TC::ZS + 4 * q + 1],
                              zbuf[lane * TC::ZS + 4 * q + 2], zbuf[lane * TC::ZS + 4 * q + 3]);
     }
+    wave_lds_sync();  // dL/dz is read before the next chunk's rows replace it
     first = false;
   }
 #pragma unroll
@@ -1538,28 +1545,34 @@ __global__ void vertex_sum_kernel(int R, int sub_log2, const float* part, float*
 template <int C, int F, int L, int ACT, int TE = 0, int FM = 0>
 struct TrainEntry {
   using TC = TrainCfg<C, F, L, ACT, TE, FM>;
-  static int waves_per_block(int H) {
-    const int fixed = TC::G::weight_bytes(H) + TC::back_bytes(H);
-    int w = (160 * 1024 - fixed) / TC::wave_bytes(H);
-    return w < 1 ? 0 : (w > kTrainWavesPerBlock ? kTrainWavesPerBlock : w);
+  // waves of wave_bytes that fit a workgroup's LDS next to the weights
+  static int waves_fit(int fixed, int wave_bytes) {
+    const int w = (160 * 1024 - fixed) / wave_bytes;
+    return w > kTrainWavesPerBlock ? kTrainWavesPerBlock : w;
   }
-  template <class TH>
-  static int waves_per_block_h(int H) {
-    const int fixed = TH::G::weight_bytes(H) + TH::back_bytes(H);
-    int w = (160 * 1024 - fixed) / TH::wave_bytes(H);
-    return w < 1 ? 0 : (w > kTrainWavesPerBlock ? kTrainWavesPerBlock : w);
-  }
-  static int n_waves(long long n) {
+  // The partition's bound (it sizes the workspace, for either precision).
+  static int max_waves(long long n) {
     const long long c = (n + TC::S - 1) / TC::S;
     const long long cap = C == 48 ? kTrainMaxWaves48 : kTrainMaxWaves;
     return (int)(c < cap ? (c < 1 ? 1 : c) : cap);
   }
-  static int n_groups(long long n) { return (n_waves(n) + kGroup - 1) / kGroup; }
+  // Waves of a launch whose workgroups hold at most `fit`, and the waves per
+  // workgroup: every wave resident at once (a workgroup takes a whole CU's
+  // LDS, so a launch of more workgroups than CUs runs a second round for the
+  // few that are left), spread over all CUs, but at least four to a
+  // workgroup, which stage its weights together.
+  static void partition(long long n, int fit, int* nw, int* wpb) {
+    const int cus = device_cus(), most = max_waves(n);
+    *nw = most < cus * fit ? most : cus * fit;
+    const int spread = (*nw + cus - 1) / cus, least = fit < 4 ? fit : 4;
+    *wpb = spread < least ? least : spread;
+  }
+  static int n_groups(int nw) { return (nw + kGroup - 1) / kGroup; }
   // wave slices, then the group partials of the reduction, then the per-point
   // dL/dz [n][F], cells [n], sorted order [n] and ranks within the cell [n],
   // and per cell the point counts and the offsets (+1)
   static size_t slices_bytes(const NetDev& nd, long long n) {
-    return ((size_t)(n_waves(n) + n_groups(n)) * TC::slice(nd.H) * sizeof(float) + 15) / 16 * 16;
+    return ((size_t)(max_waves(n) + n_groups(max_waves(n))) * TC::slice(nd.H) * sizeof(float) + 15) / 16 * 16;
   }
   static size_t ws_bytes(const NetDev& nd, long long n) {
     const long long ncell = (long long)(nd.R - 1) * (nd.R - 1) * (nd.R - 1);
@@ -1571,8 +1584,10 @@ struct TrainEntry {
                  bool half, hipStream_t st) {
     const int H = nd.H;
     if (half && (!half_train_ok<C, F, L, TE, FM>() || !target)) return 1;
-    const int wpb = waves_per_block(H);
-    if (wpb < 1) return kLaunchNoLds;
+    const int fit = waves_fit(TC::G::weight_bytes(H) + TC::back_bytes(H), TC::wave_bytes(H));
+    if (fit < 1) return kLaunchNoLds;
+    int nw, wpb;
+    partition(n, fit, &nw, &wpb);
     const int ncell = (nd.R - 1) * (nd.R - 1) * (nd.R - 1);
     char* wsb = (char*)ws + slices_bytes(nd, n);
     float* dz = (float*)wsb;
@@ -1586,7 +1601,6 @@ struct TrainEntry {
                        (long long)ncell, 0.0f);  // zero bits: zero counts
     int rc = check_launch();
     if (rc) return rc;
-    const int nw = n_waves(n);
     const size_t shm = (size_t)TC::block_bytes(H, wpb);
     static bool attr = false;
     if (!attr) {
@@ -1600,8 +1614,9 @@ struct TrainEntry {
     if (n > 0 && half) {
       if constexpr (half_train_ok<C, F, L, TE, FM>()) {
         using TH = TrainCfgH<C, F, L, ACT>;
-        const int wph = waves_per_block_h<TH>(H);
-        if (wph < 1) return kLaunchNoLds;
+        const int fit_h = waves_fit(TH::G::weight_bytes(H) + TH::back_bytes(H), TH::wave_bytes(H));
+        if (fit_h < 1) return kLaunchNoLds;
+        partition(n, fit_h, &nw, &wpb);
         static bool attr_h = false;
         if (!attr_h) {
           (void)hipFuncSetAttribute((const void*)fwd_bwd_h_kernel<C, F, L, ACT>,
@@ -1611,8 +1626,8 @@ struct TrainEntry {
         // dL/dy scaled by gs = 2^floor(log2 n) for FP16, gradients by 1 / gs
         const int e = std::ilogb((double)n);
         const double gs = std::ldexp(1.0, e);
-        hipLaunchKernelGGL((fwd_bwd_h_kernel<C, F, L, ACT>), dim3((nw + wph - 1) / wph), dim3(wph * 64),
-                           (size_t)TH::block_bytes(H, wph), st, nd2, kt, xyz, times, n, target, target_grad,
+        hipLaunchKernelGGL((fwd_bwd_h_kernel<C, F, L, ACT>), dim3((nw + wpb - 1) / wpb), dim3(wpb * 64),
+                           (size_t)TH::block_bytes(H, wpb), st, nd2, kt, xyz, times, n, target, target_grad,
                            grad_weight / 3.0f, dz, cell, count, rank, (float*)ws, nw, (float)(gs / (double)n),
                            (float)(1.0 / gs));
         rc = check_launch();
@@ -1647,7 +1662,7 @@ struct TrainEntry {
                          (const int*)cell, (const int*)rank, (const int*)off, n, order);
       if ((rc = check_launch())) return rc;
     }
-    const int sl = TC::slice(H), ng = n_groups(n);
+    const int sl = TC::slice(H), ng = n_groups(nw);
     float* partial = (float*)ws + (size_t)nw * sl;
     hipLaunchKernelGGL(slice_sum_kernel, dim3((sl + 255) / 256, ng), dim3(256), 0, st, (const float*)ws, nw, sl,
                        partial);
