@@ -70,7 +70,7 @@ struct TrainCfg {
   static_assert(4 * S <= 64, "four outputs of S samples must fit the dL/dy buffer");
   static_assert(S * ZS * 4 <= FEAT, "dL/dz must fit the input rows");
   static constexpr int BACC = MT * 4 * 16;          // one layer's bias sums: [M-tile][row group] f4
-  __host__ __device__ static int wave_bytes(int H) { return FEAT + abuf_bytes(H) + DY + (H - 1) * BACC; }
+  __host__ __device__ static int wave_bytes(int H) { return FEAT + abuf_bytes(H) + DY; }
   // The backward pass needs W^T. For c = 32 a transposed copy of each hidden
   // layer and of W_0's latent columns is staged once per workgroup (14 KiB at
   // H = 4: one wave of seven fewer per CU, but lane-contiguous reads); wider
@@ -82,9 +82,19 @@ struct TrainCfg {
   static constexpr int WB = MT * 4 * MT * 64 * 4;   // one hidden layer's W^T
   static constexpr int WZ = 4 * MT * 64 * 4;        // latent columns of W_0, transposed
   __host__ __device__ static int back_bytes(int H) { return kBackCopy ? (H - 1) * WB + WZ : 0; }
-  __host__ __device__ static int block_bytes(int H, int waves) {
-    return G::weight_bytes(H) + back_bytes(H) + waves * wave_bytes(H);
+  // the waves' bias sums, behind the weights and the waves' buffers, and behind
+  // the buffers of the waves' sum at the kernel's end (sum_waves)
+  __host__ __device__ static int bias_at(int H, int waves) {
+    const int a = G::weight_bytes(H) + back_bytes(H) + waves * wave_bytes(H),
+              b = kBlockSum ? waves / 2 * slice(H) * 4 : 0;
+    return a > b ? a : b;
   }
+  __host__ __device__ static int block_bytes(int H, int waves) { return bias_at(H, waves) + waves * (H - 1) * BACC; }
+  // One slice per workgroup (sum_waves) in FP32 at c = 32. Wider networks hold most
+  // tiles in their slices anyway, and summing those at the kernel's end costs
+  // more than the launch that sums a slice per wave (c = 48: 380 against 372 us
+  // per FP16 step).
+  static constexpr bool kBlockSum = C == 32;
   // workspace slice (floats)
   __host__ __device__ static int tiles(int H) { return MT * NK0 + (H - 1) * MT * MT + MT + (H - 1) * MT; }
   // after the tiles: per-lane partials of the four output biases, then of the loss
@@ -251,6 +261,37 @@ __device__ inline void write_row_quad(typename CF::E* row, const LatentSrc& ls, 
   }
 }
 
+// Sums the waves of a workgroup into its first wave, in a fixed tree order:
+// per level the upper half of the waves leave their values in LDS and the
+// lower half add them. `visit(fn)` calls fn(offset, f4&) for every tile the
+// wave holds (offset in the slice, in floats) and visit_f(fn) fn(offset,
+// float&) for its per-lane partials; bias sums stay in the waves' own LDS areas
+// (bacc, n_bias f4s, bias_stride f4s from a wave to the next), which the level
+// buffers at `area` must not overlap. Every wave of the workgroup calls it.
+// One slice per workgroup leaves the launch instead of one per wave (study
+// network, 2^18 points: 8 MB instead of 66, written and read back).
+template <class VisitTile, class VisitFloat>
+__device__ inline void sum_waves(float* area, int slice, int waves, int wave_l, int lane, f4* bacc, int n_bias,
+                                 int bias_stride, VisitTile visit, VisitFloat visit_f) {
+  for (int n = waves; n > 1;) {
+    const int half = (n + 1) / 2;
+    __syncthreads();  // the level before has been read
+    if (wave_l >= half && wave_l < n) {
+      float* a = area + (size_t)(wave_l - half) * slice;
+      visit([&](int at, f4& v) { reinterpret_cast<f4*>(a + at)[lane] = v; });
+      visit_f([&](int at, float& v) { a[at + lane] = v; });
+    }
+    __syncthreads();
+    if (wave_l < n - half) {
+      const float* a = area + (size_t)wave_l * slice;
+      visit([&](int at, f4& v) { v += reinterpret_cast<const f4*>(a + at)[lane]; });
+      visit_f([&](int at, float& v) { v += a[at + lane]; });
+      for (int e = lane; e < n_bias; e += kWave) bacc[e] += bacc[e + half * bias_stride];
+    }
+    n = half;
+  }
+}
+
 template <int C, int F, int L, int ACT, int TE, int FM>
 __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDev nd, KeyTimes kt, const float* xyz,
                                                                             const float* times, long long n,
@@ -272,7 +313,6 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
   __syncthreads();
   const int wave_l = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wave = blockIdx.x * (blockDim.x >> 6) + wave_l;
-  if (wave >= n_waves) return;
   const int g = lane >> 4, nn = lane & 15;
   char* wbase = back + TC::back_bytes(H) + wave_l * TC::wave_bytes(H);
   float* feat = reinterpret_cast<float*>(wbase);
@@ -281,7 +321,8 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
   float* zbuf = feat;  // dL/dz, over the input rows
   // bias gradients of the hidden layers, summed over the chunk's points in the
   // wave and accumulated here over its chunks ([layer][M-tile][row group])
-  f4* bacc = reinterpret_cast<f4*>(wbase + TC::FEAT + TC::abuf_bytes(H) + TC::DY);
+  const int waves = blockDim.x >> 6;
+  f4* bacc = reinterpret_cast<f4*>(smem + TC::bias_at(H, waves) + wave_l * (H - 1) * TC::BACC);
   for (int e = lane; e < (H - 1) * MT * 4; e += kWave) bacc[e] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   float* slice = ws + (size_t)wave * TC::slice(H);
   const float* W0 = reinterpret_cast<const float*>(smem);
@@ -349,7 +390,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
 #pragma unroll
   for (int k = 0; k < NRH; ++k) accH[k] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   load_point(wave);
-  for (long long c = wave; c < nchunks; c += n_waves) {
+  for (long long c = wave < n_waves ? wave : nchunks; c < nchunks; c += n_waves) {
     // lane l < S owns point c * S + l
     const long long idx = c * S + lane;
     const bool ok = lane < S && idx < n;
@@ -635,18 +676,48 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
     wave_lds_sync();  // dL/dz is read before the next chunk's rows replace it
     first = false;
   }
+  // ---------------- the workgroup's sums, into its first wave's slice
+  const bool mine = wave < n_waves;
+  auto resident = [&](auto fn) {
 #pragma unroll
-  for (int k = 0; k < NR0; ++k)
-    reinterpret_cast<f4*>(slice + TC::tile_l0(k / TC::NK0, k % TC::NK0) * 256)[lane] = acc0[k];
-  if constexpr (kResident0) {
-    if (H >= 2) {
+    for (int k = 0; k < NR0; ++k) fn(TC::tile_l0(k / TC::NK0, k % TC::NK0) * 256, acc0[k]);
+    if constexpr (kResident0) {
+      if (H >= 2) {
 #pragma unroll
-      for (int k = 0; k < MT * MT; ++k)
-        reinterpret_cast<f4*>(slice + TC::tile_h(H, H - 1, k / MT, k % MT) * 256)[lane] = accH[k];
+        for (int k = 0; k < MT * MT; ++k) fn(TC::tile_h(H, H - 1, k / MT, k % MT) * 256, accH[k]);
+      }
     }
-  }
 #pragma unroll
-  for (int k = 0; k < MT; ++k) reinterpret_cast<f4*>(slice + TC::tile_out(H, k) * 256)[lane] = accO[k];
+    for (int k = 0; k < MT; ++k) fn(TC::tile_out(H, k) * 256, accO[k]);
+  };
+  if constexpr (TC::kBlockSum) {
+    auto in_slice = [&](auto fn) {  // tiles summed in the wave's own slice
+      auto one = [&](int t) {
+        f4* at = reinterpret_cast<f4*>(slice + t * 256) + lane;
+        f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (mine) v = *at;
+        fn(t * 256, v);
+        if (mine) *at = v;
+      };
+      for (int t = R0 * TC::NK0; t < MT * TC::NK0; ++t) one(t);
+      for (int t = MT * TC::NK0; t < TC::tile_h(H, kResident0 ? H - 1 : H, 0, 0) && H > 1; ++t) one(t);
+    };
+    sum_waves(reinterpret_cast<float*>(smem), TC::slice(H), waves, wave_l, lane, bacc, (H - 1) * MT * 4,
+              (H - 1) * MT * 4, [&](auto fn) { resident(fn); in_slice(fn); },
+              [&](auto fn) {
+#pragma unroll
+                for (int o = 0; o < 4; ++o) {
+                  float v = dbo_acc[o];
+                  fn(TC::tiles(H) * 256 + 64 * o, v);
+                  dbo_acc[o] = v;
+                }
+                fn(TC::tiles(H) * 256 + 256, loss_acc);
+              });
+    if (wave_l != 0) return;
+  } else if (!mine) {
+    return;
+  }
+  resident([&](int at, f4& v) { reinterpret_cast<f4*>(slice + at)[lane] = v; });
   // the bias sums into the slice's per-lane partial layout: lane 16 g holds
   // row group g's sums, the row's other lanes zero
   for (int i = 1; i < H; ++i)
@@ -656,7 +727,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_kernel(NetDe
       const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
       reinterpret_cast<f4*>(slice + TC::tile_bias(H, i, mt) * 256)[lane] = nn == 0 ? b : zero4;
     }
-  // ---------------- per-wave partials of the output biases and the loss
+  // ---------------- per-lane partials of the output biases and the loss
 #pragma unroll
   for (int o = 0; o < 4; ++o) slice[TC::tiles(H) * 256 + 64 * o + lane] = dbo_acc[o];
   slice[TC::tiles(H) * 256 + 256 + lane] = loss_acc;
@@ -770,7 +841,6 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_h_kernel(
   __syncthreads();
   const int wave_l = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wave = blockIdx.x * (blockDim.x >> 6) + wave_l;
-  if (wave >= n_waves) return;
   const int g = lane >> 4, nn = lane & 15;
   char* wbase = back + TH::back_bytes(H) + wave_l * TH::wave_bytes(H);
   E* feat = reinterpret_cast<E*>(wbase);
@@ -833,7 +903,7 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_h_kernel(
 #pragma unroll
   for (int k = 0; k < NRH; ++k) accH[k] = accH2[k] = zero;
   load_point(wave);
-  for (long long c = wave; c < nchunks; c += n_waves) {
+  for (long long c = wave < n_waves ? wave : nchunks; c < nchunks; c += n_waves) {
     const long long idx = c * S + lane;
     const bool ok = lane < S && idx < n;
     const float px = npx, py = npy, pz = npz, pt = npt, tg = ntg;
@@ -1091,6 +1161,11 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_h_kernel(
     }
     first = false;
   }
+  // ---------------- the wave's sums into its slice. (Not summed over the
+  // workgroup first: that is 17 us faster per 2^18-point step, but weights that
+  // differ in their last bit after an update fall to other FP16 values, and
+  // the FP16 passes carry the order of these sums into later steps.)
+  if (wave >= n_waves) return;
 #pragma unroll
   for (int k = 0; k < NR0; ++k)
     reinterpret_cast<f4*>(slice + T32::tile_l0(k / T32::NK0, k % T32::NK0) * 256)[lane] = acc0[k];
@@ -1120,123 +1195,79 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_h_kernel(
   slice[T32::tiles(H) * 256 + 256 + lane] = loss_acc;
 }
 
-// Sums the wave slices in a fixed order into the packed gradient, in two
-// stages so that the reads are coalesced and plenty of them are in flight:
-// slice_sum_kernel adds groups of kGroup consecutive slices element-wise
-// (partial[g][e], threads along e), gather_kernel then locates every weight's
-// terms in the slice layout and adds them over the groups. Both orders are
-// fixed, so the result is bitwise reproducible.
-constexpr int kGroup = 256;
-
-__global__ void slice_sum_kernel(const float* ws, int n_waves, int sl, float* partial) {
+// Sums the workgroups' slices (`stride` floats apart) in a fixed order into
+// the packed gradient, in two stages so that the reads are coalesced and
+// plenty of them are in flight: slice_sum_kernel adds groups of slices
+// element-wise (partial[g][e], threads along e), gather_kernel then locates
+// every weight's terms in the slice layout and adds them over the groups. Both
+// orders are fixed, so the result is bitwise reproducible.
+__global__ void slice_sum_kernel(const float* ws, int n, size_t stride, int sl, int group, float* partial) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   const int g = blockIdx.y;
   if (e >= sl) return;
-  const int w0 = g * kGroup, w1 = min(w0 + kGroup, n_waves);
+  const int w0 = g * group, w1 = min(w0 + group, n);
   // eight independent partial sums keep eight loads in flight; they are
   // combined in a fixed order
   float s8[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   int w = w0;
   for (; w + 8 <= w1; w += 8)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s8[k] += ws[(size_t)(w + k) * sl + e];
-  for (; w < w1; ++w) s8[0] += ws[(size_t)w * sl + e];
+    for (int k = 0; k < 8; ++k) s8[k] += ws[(size_t)(w + k) * stride + e];
+  for (; w < w1; ++w) s8[0] += ws[(size_t)w * stride + e];
   partial[(size_t)g * sl + e] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
 }
 
-template <int C, int F, int L, int ACT, int TE, int FM>
-__global__ void gather_kernel(int H, int NO, const float* partial, int n_groups, float* d_weights, float* out_loss,
-                              float loss_scale) {
-  using TC = TrainCfg<C, F, L, ACT, TE, FM>;
-  using G = typename TC::G;
-  const int K0 = G::K0IN;
-  const long long nw = (long long)C * K0 + C + (long long)(H - 1) * (C * C + C) + (long long)NO * (C + 1);
-  const int SL = TC::slice(H);
-  for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < nw + 1;
-       j += (long long)gridDim.x * blockDim.x) {
-    // locate weight j: a list of (offset within slice) terms to add
-    int base = -1, count = 0, stride = 0;
-    if (j == nw) {  // loss
-      base = TC::tiles(H) * 256 + 256;
-      count = 64;
-      stride = 1;
-    } else {
-      long long r = j;
-      const long long l0 = (long long)C * K0;
-      if (r < l0 + C) {
-        int o, col;
-        if (r < l0) {
-          o = (int)(r / K0);
-          const int k = (int)(r % K0);
-          col = G::feat_col(k);
-        } else {
-          o = (int)(r - l0);
-          col = G::KMAIN + 3;
-        }
-        const int tile = TC::tile_l0(o / 16, col / 16);
-        base = tile * 256 + (16 * ((o % 16) / 4) + col % 16) * 4 + o % 4;
-        count = 1;
-      } else {
-        r -= l0 + C;
-        const long long per = (long long)C * C + C;
-        const int i = 1 + (int)(r / per);
-        if (i < H) {
-          r %= per;
-          if (r < (long long)C * C) {
-            const int o = (int)(r / C), k = (int)(r % C);
-            base = TC::tile_h(H, i, o / 16, k / 16) * 256 + (16 * ((o % 16) / 4) + k % 16) * 4 + o % 4;
-            count = 1;
-          } else {
-            const int o = (int)(r - (long long)C * C);
-            base = TC::tile_bias(H, i, o / 16) * 256 + (16 * ((o % 16) / 4)) * 4 + o % 4;
-            count = 16;
-            stride = 4;
-          }
-        } else {
-          r -= (long long)(H - 1) * per;
-          if (r < (long long)NO * C) {
-            // W_out[o][k]: row o of the output tile, held by lane k % 16
-            const int o = (int)(r / C), k = (int)(r % C);
-            base = TC::tile_out(H, k / 16) * 256 + (k % 16) * 4 + o;
-            count = 1;
-          } else {
-            base = TC::tiles(H) * 256 + 64 * (int)(r - (long long)NO * C);
-            count = 64;
-            stride = 1;
-          }
-        }
-      }
-    }
-    // sums of 16 or 64 terms per group (the hidden and output biases, the
-    // loss) are gather_long_kernel's
-    if (count > 1) continue;
-    // sequential adds in a fixed order
-    float s = 0.0f;
-    for (int g = 0; g < n_groups; ++g) {
-      const float* pg = partial + (size_t)g * SL + base;
-#pragma unroll 8
-      for (int c = 0; c < count; ++c) s += pg[c * stride];
-    }
-    if (j == nw) {
-      if (out_loss) *out_loss = s * loss_scale;
-    } else {
-      d_weights[j] = s;
-    }
+// Bias-corrected Adam (PyTorch's form): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
+// p -= lr / bc1 * m / (sqrt(v) / sqrt(bc2) + eps). The kernels that write the
+// weights' and the two-pass latent gradient apply it to the parameter of each
+// entry as they write it (p null: gradients only); the one-pass latent
+// gradient, written by one lane in eight, leaves it to a launch of its own
+// (keyframe network, 2^18 points: 382 us against 399).
+struct AdamDev {
+  float *p, *m, *v;
+  float lr_bc1, b1, b2, inv_sqrt_bc2, eps;
+};
+
+__device__ inline void adam_update(const AdamDev& a, long long i, float gi) {
+  const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  a.p[i] -= a.lr_bc1 * mi / (sqrtf(vi) * a.inv_sqrt_bc2 + a.eps);
+}
+
+// The same on four neighbouring entries.
+__device__ inline void adam_update4(const AdamDev& a, long long i, f4 g) {
+  f4 m = *reinterpret_cast<const f4*>(a.m + i), v = *reinterpret_cast<const f4*>(a.v + i),
+     p = *reinterpret_cast<const f4*>(a.p + i);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    m[j] = a.b1 * m[j] + (1.0f - a.b1) * g[j];
+    v[j] = a.b2 * v[j] + (1.0f - a.b2) * g[j] * g[j];
+    p[j] -= a.lr_bc1 * m[j] / (sqrtf(v[j]) * a.inv_sqrt_bc2 + a.eps);
   }
+  *reinterpret_cast<f4*>(a.m + i) = m;
+  *reinterpret_cast<f4*>(a.v + i) = v;
+  *reinterpret_cast<f4*>(a.p + i) = p;
+}
+
+// Adam over n4 groups of four entries.
+__global__ void adam_kernel(const float* g, long long n4, AdamDev adam) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (long long)gridDim.x * blockDim.x)
+    adam_update4(adam, 4 * i, reinterpret_cast<const f4*>(g)[i]);
 }
 
 // The weights whose gradient sums many partials per group, one wave each:
 // the hidden-layer biases (16 lane partials per group), the output biases and
 // the loss (64). Lane l adds its term over the groups in order, then the wave
 // adds the lanes in a fixed butterfly, so the result is bitwise reproducible.
-template <int C, int F, int L, int ACT, int TE, int FM>
-__global__ __launch_bounds__(64) void gather_long_kernel(int H, int NO, const float* partial, int n_groups,
-                                                          float* d_weights, float* out_loss, float loss_scale) {
-  using TC = TrainCfg<C, F, L, ACT, TE, FM>;
-  using G = typename TC::G;
-  const int e = blockIdx.x, lane = threadIdx.x;
+template <class TC>
+__device__ inline void gather_long(int e, int H, int NO, const float* partial, int n_groups, float* d_weights,
+                                   float* out_loss, float loss_scale, const AdamDev& adam) {
+  constexpr int C = TC::CF::C;
+  const int lane = threadIdx.x & 63;
   const int SL = TC::slice(H);
-  const long long first_bias = (long long)C * G::K0IN + C;  // W_1 in the packed weights
+  const long long first_bias = (long long)C * TC::G::K0IN + C;  // W_1 in the packed weights
   const long long per = (long long)C * C + C;
   int base, count, stride;
   long long j;  // destination weight (-1: the loss)
@@ -1267,7 +1298,76 @@ __global__ __launch_bounds__(64) void gather_long_kernel(int H, int NO, const fl
       if (out_loss) *out_loss = a * loss_scale;
     } else {
       d_weights[j] = a;
+      if (adam.p) adam_update(adam, j, a);
     }
+  }
+}
+
+constexpr int kGatherThreads = 128;
+
+// Workgroups [0, n_short) take a weight per thread, the others gather_long's
+// entries, one per wave.
+template <int C, int F, int L, int ACT, int TE, int FM>
+__global__ __launch_bounds__(kGatherThreads) void gather_kernel(int H, int NO, const float* partial, int n_groups,
+                                                                float* d_weights, float* out_loss, float loss_scale,
+                                                                int n_short, AdamDev adam) {
+  using TC = TrainCfg<C, F, L, ACT, TE, FM>;
+  using G = typename TC::G;
+  if ((int)blockIdx.x >= n_short) {
+    const int e = ((int)blockIdx.x - n_short) * (kGatherThreads / 64) + (int)(threadIdx.x >> 6);
+    if (e < (H - 1) * C + NO + 1)
+      gather_long<TC>(e, H, NO, partial, n_groups, d_weights, out_loss, loss_scale, adam);
+    return;
+  }
+  const int K0 = G::K0IN;
+  const long long nw = (long long)C * K0 + C + (long long)(H - 1) * (C * C + C) + (long long)NO * (C + 1);
+  const int SL = TC::slice(H);
+  for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < nw;
+       j += (long long)n_short * blockDim.x) {
+    // locate weight j: a list of (offset within slice) terms to add
+    int base = -1;
+    {
+      long long r = j;
+      const long long l0 = (long long)C * K0;
+      if (r < l0 + C) {
+        int o, col;
+        if (r < l0) {
+          o = (int)(r / K0);
+          const int k = (int)(r % K0);
+          col = G::feat_col(k);
+        } else {
+          o = (int)(r - l0);
+          col = G::KMAIN + 3;
+        }
+        const int tile = TC::tile_l0(o / 16, col / 16);
+        base = tile * 256 + (16 * ((o % 16) / 4) + col % 16) * 4 + o % 4;
+      } else {
+        r -= l0 + C;
+        const long long per = (long long)C * C + C;
+        const int i = 1 + (int)(r / per);
+        if (i < H) {
+          r %= per;
+          if (r < (long long)C * C) {
+            const int o = (int)(r / C), k = (int)(r % C);
+            base = TC::tile_h(H, i, o / 16, k / 16) * 256 + (16 * ((o % 16) / 4) + k % 16) * 4 + o % 4;
+          }
+        } else {
+          r -= (long long)(H - 1) * per;
+          if (r < (long long)NO * C) {
+            // W_out[o][k]: row o of the output tile, held by lane k % 16
+            const int o = (int)(r / C), k = (int)(r % C);
+            base = TC::tile_out(H, k / 16) * 256 + (k % 16) * 4 + o;
+          }
+        }
+      }
+    }
+    if (base < 0) continue;  // a bias: gather_long's
+    // sequential adds in a fixed order
+    float s = 0.0f;
+#pragma unroll 8
+    for (int g = 0; g < n_groups; ++g) s += partial[(size_t)g * SL + base];
+    d_weights[j] = s;
+    if (adam.p) adam_update(adam, j, s);
   }
 }
 
@@ -1276,28 +1376,17 @@ __global__ void fill_kernel(float* p, long long n, float v) {
     p[i] = v;
 }
 
-// Bias-corrected Adam (PyTorch's form): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
-// p -= lr / bc1 * m / (sqrt(v) / sqrt(bc2) + eps).
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v, long long n, float lr_bc1, float b1,
-                            float b2, float inv_sqrt_bc2, float eps) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr_bc1 * mi / (sqrtf(vi) * inv_sqrt_bc2 + eps);
-  }
-}
-
 // ------------------------------------------ latent gradient by gathering
 
 // Exclusive prefix sums of the per-cell point counts, off[c] = first sorted
-// position of cell c, off[ncell] = n, cursor (when given) a copy of off: blocks of
-// kCellBlock consecutive cells are summed (cell_block_sum_kernel), the block
-// sums scanned by one workgroup (cell_block_scan_kernel), then every block
-// scans its own cells from its block's offset (cell_scan_kernel).
-constexpr int kCellThreads = 256, kCellItems = 16, kCellBlock = kCellThreads * kCellItems;
+// position of cell c, off[ncell] = n, by blocks of kCellBlock consecutive
+// cells. Up to kSelfScanBlocks of them (a 32^3 grid has 8) each block adds the
+// counts of all cells before it itself, four per thread and step (one launch of
+// 6 us instead of three of 4 to 5); beyond (64^3: 62), the blocks are summed
+// (cell_block_sum_kernel) and the block sums scanned by one workgroup
+// (cell_block_scan_kernel) first.
+constexpr int kCellThreads = 1024, kCellItems = 4, kCellBlock = kCellThreads * kCellItems;
+constexpr int kSelfScanBlocks = 16;
 
 int cell_blocks(long long ncell) { return (int)((ncell + kCellBlock - 1) / kCellBlock); }
 
@@ -1367,12 +1456,24 @@ __global__ __launch_bounds__(kBlockScanThreads) void cell_block_scan_kernel(int*
   if (threadIdx.x == 0) *off_end = carry;
 }
 
-// Block b: its cells' exclusive prefix sums from its block offset (bsum,
-// or 0 when bsum is null); each thread takes kCellItems consecutive cells.
-// With a single block (off_end set) the kernel also writes the total.
+// Block b: its cells' exclusive prefix sums from its block offset (bsum, or,
+// when bsum is null, the sum of the counts before it); each thread takes
+// kCellItems consecutive cells. off_end (null if cell_block_scan_kernel has
+// written it) receives the total.
 __global__ __launch_bounds__(kCellThreads) void cell_scan_kernel(const int* count, int ncell, const int* bsum, int* off,
-                                                                 int* cursor, int* off_end) {
+                                                                 int* off_end) {
   __shared__ int wsum[kCellThreads / 64];
+  int before = bsum ? bsum[blockIdx.x] : 0;
+  if (!bsum && blockIdx.x > 0) {
+    const int4* c4 = reinterpret_cast<const int4*>(count);
+    int s = 0;
+#pragma unroll 8
+    for (int k = threadIdx.x; k < (int)blockIdx.x * (kCellBlock / 4); k += kCellThreads) {
+      const int4 c = c4[k];
+      s += (c.x + c.y) + (c.z + c.w);
+    }
+    (void)block_exclusive_scan<kCellThreads>(s, wsum, &before);
+  }
   const int base = blockIdx.x * kCellBlock + threadIdx.x * kCellItems;
   int x[kCellItems], sum = 0;
 #pragma unroll
@@ -1381,16 +1482,13 @@ __global__ __launch_bounds__(kCellThreads) void cell_scan_kernel(const int* coun
     sum += x[k];
   }
   int total;
-  int run = (bsum ? bsum[blockIdx.x] : 0) + block_exclusive_scan<kCellThreads>(sum, wsum, &total);
+  int run = before + block_exclusive_scan<kCellThreads>(sum, wsum, &total);
 #pragma unroll
   for (int k = 0; k < kCellItems; ++k) {
-    if (base + k < ncell) {
-      off[base + k] = run;
-      if (cursor) cursor[base + k] = run;
-    }
+    if (base + k < ncell) off[base + k] = run;
     run += x[k];
   }
-  if (off_end && threadIdx.x == 0) *off_end = total;
+  if (off_end && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *off_end = before + total;
 }
 
 // Counting sort: point i goes to the slot its cell count gave it when the
@@ -1431,28 +1529,53 @@ __global__ void latent_grad_kernel(const float* xyz, const float* times, KeyTime
     for (int f = 0; f < F; ++f) acc[f] = 0.0f;
     if (cx >= 0 && cx <= R - 2 && cy >= 0 && cy <= R - 2 && cz >= 0 && cz <= R - 2) {
       const int c = (cz * (R - 1) + cy) * (R - 1) + cx;
-      for (int s = off[c] + sub; s < off[c + 1]; s += lpc) {
-        const int p = order[s];
-        int ix, iy, iz;
-        float fx, fy, fz;
-        axis_cell(xyz[3 * p], R, ix, fx);
-        axis_cell(xyz[3 * p + 1], R, iy, fy);
-        axis_cell(xyz[3 * p + 2], R, iz, fz);
-        float w = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz);
-        if (K > 1) {
-          int key;
-          float kw;
-          key_pair(kt, K, times ? times[p] : 0.0f, key, kw);
-          w *= (k == key ? 1.0f - kw : 0.0f) + (k == key + 1 ? kw : 0.0f);
-        }
-        const float4* src = reinterpret_cast<const float4*>(dz + (long long)p * F);
+      // two points at a time, so that their loads are in flight together
+      const int end = off[c + 1];
+      for (int s = off[c] + sub; s < end; s += 2 * lpc) {
+        int p[2];
+        float x[2][3], t[2], w[2];
 #pragma unroll
-        for (int q = 0; q < F / 4; ++q) {
-          const float4 d4 = src[q];
-          acc[4 * q] = fmaf(w, d4.x, acc[4 * q]);
-          acc[4 * q + 1] = fmaf(w, d4.y, acc[4 * q + 1]);
-          acc[4 * q + 2] = fmaf(w, d4.z, acc[4 * q + 2]);
-          acc[4 * q + 3] = fmaf(w, d4.w, acc[4 * q + 3]);
+        for (int i = 0; i < 2; ++i) p[i] = order[s + i * lpc < end ? s + i * lpc : s];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) x[i][a] = xyz[3 * (long long)p[i] + a];
+          t[i] = K > 1 && times ? times[p[i]] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          int ix, iy, iz;
+          float fx, fy, fz;
+          axis_cell(x[i][0], R, ix, fx);
+          axis_cell(x[i][1], R, iy, fy);
+          axis_cell(x[i][2], R, iz, fz);
+          w[i] = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz);
+          if (K > 1) {
+            int key;
+            float kw;
+            key_pair(kt, K, t[i], key, kw);
+            w[i] *= (k == key ? 1.0f - kw : 0.0f) + (k == key + 1 ? kw : 0.0f);
+          }
+        }
+        // a point of other keyframes (weight zero) is not read further
+        f4 d[2][F / 4];
+        bool on[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          on[i] = s + i * lpc < end && (K == 1 || w[i] != 0.0f);
+          if (on[i]) {
+#pragma unroll
+            for (int q = 0; q < F / 4; ++q) d[i][q] = reinterpret_cast<const f4*>(dz + (long long)p[i] * F)[q];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (on[i]) {
+#pragma unroll
+            for (int q = 0; q < F / 4; ++q)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) acc[4 * q + j] = fmaf(w[i], d[i][q][j], acc[4 * q + j]);
+          }
         }
       }
     }
@@ -1498,20 +1621,36 @@ __global__ void cell_partials_kernel(const float* xyz, int R, long long ncell, i
     f4 acc[8];
 #pragma unroll
     for (int b = 0; b < 8; ++b) acc[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s = off[c] + sub; s < off[c + 1]; s += nsub) {
-      const int p = order[s];
-      int ix, iy, iz;
-      float fx, fy, fz;
-      axis_cell(xyz[3 * p], R, ix, fx);
-      axis_cell(xyz[3 * p + 1], R, iy, fy);
-      axis_cell(xyz[3 * p + 2], R, iz, fz);
-      const f4 d = reinterpret_cast<const f4*>(dz + (long long)p * F)[qd];
+    // four points at a time, so that their loads are in flight together; past
+    // the last one a point is read again with weight zero
+    const int end = off[c + 1];
+    for (int s = off[c] + sub; s < end; s += 4 * nsub) {
+      int p[4];
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const int bx = b & 1, by = (b >> 1) & 1, bz = b >> 2;
-        const float w = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz);
+      for (int k = 0; k < 4; ++k) p[k] = order[s + k * nsub < end ? s + k * nsub : s];
+      float x[4][3];
+      f4 d[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[b][j] = fmaf(w, d[j], acc[b][j]);
+      for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) x[k][a] = xyz[3 * (long long)p[k] + a];
+        d[k] = reinterpret_cast<const f4*>(dz + (long long)p[k] * F)[qd];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        int ix, iy, iz;
+        float fx, fy, fz;
+        axis_cell(x[k][0], R, ix, fx);
+        axis_cell(x[k][1], R, iy, fy);
+        axis_cell(x[k][2], R, iz, fz);
+        const float on = s + k * nsub < end ? 1.0f : 0.0f;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const int bx = b & 1, by = (b >> 1) & 1, bz = b >> 2;
+          const float w = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz) * on;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[b][j] = fmaf(w, d[k][j], acc[b][j]);
+        }
       }
     }
 #pragma unroll
@@ -1520,7 +1659,7 @@ __global__ void cell_partials_kernel(const float* xyz, int R, long long ncell, i
 }
 
 template <int F>
-__global__ void vertex_sum_kernel(int R, int sub_log2, const float* part, float* d_latent) {
+__global__ void vertex_sum_kernel(int R, int sub_log2, const float* part, float* d_latent, AdamDev adam) {
   constexpr int NQ = F / 4;
   const long long nv = (long long)R * R * R;
   for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < nv * NQ;
@@ -1539,16 +1678,19 @@ __global__ void vertex_sum_kernel(int R, int sub_log2, const float* part, float*
       }
     }
     reinterpret_cast<f4*>(d_latent + v * F)[qd] = sum;
+    if (adam.p) adam_update4(adam, v * F + 4 * qd, sum);
   }
 }
 
 template <int C, int F, int L, int ACT, int TE = 0, int FM = 0>
 struct TrainEntry {
   using TC = TrainCfg<C, F, L, ACT, TE, FM>;
-  // waves of wave_bytes that fit a workgroup's LDS next to the weights
-  static int waves_fit(int fixed, int wave_bytes) {
-    const int w = (160 * 1024 - fixed) / wave_bytes;
-    return w > kTrainWavesPerBlock ? kTrainWavesPerBlock : w;
+  // waves whose workgroup fits the LDS
+  template <class T>
+  static int waves_fit(int H) {
+    int w = kTrainWavesPerBlock;
+    while (w > 0 && T::block_bytes(H, w) > 160 * 1024) --w;
+    return w;
   }
   // The partition's bound (it sizes the workspace, for either precision).
   static int max_waves(long long n) {
@@ -1557,22 +1699,24 @@ struct TrainEntry {
     return (int)(c < cap ? (c < 1 ? 1 : c) : cap);
   }
   // Waves of a launch whose workgroups hold at most `fit`, and the waves per
-  // workgroup: every wave resident at once (a workgroup takes a whole CU's
-  // LDS, so a launch of more workgroups than CUs runs a second round for the
-  // few that are left), spread over all CUs, but at least four to a
-  // workgroup, which stage its weights together.
-  static void partition(long long n, int fit, int* nw, int* wpb) {
+  // workgroup. FP32: no more waves than are resident at once (a workgroup takes
+  // a whole CU's LDS, so a launch of more workgroups than CUs runs a second
+  // round for the few that are left); FP16 keeps the partition's bound. Spread
+  // over all CUs, but at least four to a workgroup, which stage its weights
+  // together.
+  static void partition(long long n, int fit, bool half, int* nw, int* wpb) {
     const int cus = device_cus(), most = max_waves(n);
-    *nw = most < cus * fit ? most : cus * fit;
+    *nw = half || most < cus * fit ? most : cus * fit;
     const int spread = (*nw + cus - 1) / cus, least = fit < 4 ? fit : 4;
-    *wpb = spread < least ? least : spread;
+    *wpb = spread < least ? least : (spread < fit ? spread : fit);
   }
-  static int n_groups(int nw) { return (nw + kGroup - 1) / kGroup; }
-  // wave slices, then the group partials of the reduction, then the per-point
-  // dL/dz [n][F], cells [n], sorted order [n] and ranks within the cell [n],
-  // and per cell the point counts and the offsets (+1)
+  // wave slices, then space for the group partials of the reduction, then the per-point
+  // dL/dz [n][F], per cell the point counts and the offsets (+1) and the block
+  // sums of the scan, and per point its cell, sorted order and rank within the
+  // cell
+  static int slices(long long n) { return max_waves(n) + (max_waves(n) + 255) / 256; }
   static size_t slices_bytes(const NetDev& nd, long long n) {
-    return ((size_t)(max_waves(n) + n_groups(max_waves(n))) * TC::slice(nd.H) * sizeof(float) + 15) / 16 * 16;
+    return ((size_t)slices(n) * TC::slice(nd.H) * sizeof(float) + 15) / 16 * 16;
   }
   static size_t ws_bytes(const NetDev& nd, long long n) {
     const long long ncell = (long long)(nd.R - 1) * (nd.R - 1) * (nd.R - 1);
@@ -1581,22 +1725,22 @@ struct TrainEntry {
   static int run(const NetDev& nd, const KeyTimes& kt, float* latent, float* d_latent, float* d_weights,
                  const float* xyz, const float* times, long long n, const float* target,
                  const float* target_grad, float grad_weight, const float* dloss, float* out_loss, void* ws,
-                 bool half, hipStream_t st) {
+                 bool half, const AdamDev& adam_lat, const AdamDev& adam_w, hipStream_t st) {
     const int H = nd.H;
     if (half && (!half_train_ok<C, F, L, TE, FM>() || !target)) return 1;
-    const int fit = waves_fit(TC::G::weight_bytes(H) + TC::back_bytes(H), TC::wave_bytes(H));
+    const int fit = waves_fit<TC>(H);
     if (fit < 1) return kLaunchNoLds;
     int nw, wpb;
-    partition(n, fit, &nw, &wpb);
+    partition(n, fit, false, &nw, &wpb);
     const int ncell = (nd.R - 1) * (nd.R - 1) * (nd.R - 1);
     char* wsb = (char*)ws + slices_bytes(nd, n);
     float* dz = (float*)wsb;
-    int* cell = (int*)(wsb + (size_t)n * F * 4);
-    int* order = cell + n;
-    int* rank = order + n;
-    int* count = rank + n;
+    int* count = (int*)(wsb + (size_t)n * F * 4);  // 16-byte aligned
     int* off = count + ncell;
     int* bsum = off + ncell + 1;  // cell_blocks(ncell) block sums
+    int* cell = bsum + cell_blocks(ncell);
+    int* order = cell + n;
+    int* rank = order + n;
     hipLaunchKernelGGL(fill_kernel, dim3(grid_blocks(ncell, 256, device_cus() * 8)), dim3(256), 0, st, (float*)count,
                        (long long)ncell, 0.0f);  // zero bits: zero counts
     int rc = check_launch();
@@ -1614,9 +1758,9 @@ struct TrainEntry {
     if (n > 0 && half) {
       if constexpr (half_train_ok<C, F, L, TE, FM>()) {
         using TH = TrainCfgH<C, F, L, ACT>;
-        const int fit_h = waves_fit(TH::G::weight_bytes(H) + TH::back_bytes(H), TH::wave_bytes(H));
+        const int fit_h = waves_fit<TH>(H);
         if (fit_h < 1) return kLaunchNoLds;
-        partition(n, fit_h, &nw, &wpb);
+        partition(n, fit_h, true, &nw, &wpb);
         static bool attr_h = false;
         if (!attr_h) {
           (void)hipFuncSetAttribute((const void*)fwd_bwd_h_kernel<C, F, L, ACT>,
@@ -1648,24 +1792,31 @@ struct TrainEntry {
     }
     // latent gradient: sort the points by cell, then gather per vertex
     const int nb = cell_blocks(ncell);
-    if (nb > 1) {
+    const bool summed = nb > kSelfScanBlocks;
+    if (summed) {
       hipLaunchKernelGGL(cell_block_sum_kernel, dim3(nb), dim3(kCellThreads), 0, st, (const int*)count, ncell, bsum);
       if ((rc = check_launch())) return rc;
       hipLaunchKernelGGL(cell_block_scan_kernel, dim3(1), dim3(kBlockScanThreads), 0, st, bsum, nb, off + ncell);
       if ((rc = check_launch())) return rc;
     }
     hipLaunchKernelGGL(cell_scan_kernel, dim3(nb), dim3(kCellThreads), 0, st, (const int*)count, ncell,
-                       nb > 1 ? (const int*)bsum : nullptr, off, nullptr, nb > 1 ? nullptr : off + ncell);
+                       summed ? (const int*)bsum : nullptr, off, summed ? nullptr : off + ncell);
     if ((rc = check_launch())) return rc;
     if (n > 0) {
       hipLaunchKernelGGL(bin_points_kernel, dim3(grid_blocks(n, 256, device_cus() * 8)), dim3(256), 0, st,
                          (const int*)cell, (const int*)rank, (const int*)off, n, order);
       if ((rc = check_launch())) return rc;
     }
-    const int sl = TC::slice(H), ng = n_groups(nw);
+    const int sl = TC::slice(H), per = TC::kBlockSum && !half ? wpb : 1, count_sl = (nw + per - 1) / per;
+    // the group partials go behind the launch's slices: groups of 32 slices (of
+    // 256 for a slice per wave: the order of the FP16 step's sums), larger ones
+    // where that space is short
+    const int space = slices(n) - nw, least = (count_sl + space - 1) / space, want = per > 1 ? 32 : 256;
+    const int group = least > want ? least : want;
+    const int ng = (count_sl + group - 1) / group;
     float* partial = (float*)ws + (size_t)nw * sl;
-    hipLaunchKernelGGL(slice_sum_kernel, dim3((sl + 255) / 256, ng), dim3(256), 0, st, (const float*)ws, nw, sl,
-                       partial);
+    hipLaunchKernelGGL(slice_sum_kernel, dim3((sl + 255) / 256, ng), dim3(256), 0, st, (const float*)ws, count_sl,
+                       (size_t)per * sl, sl, group, partial);
     rc = check_launch();
     if (rc) return rc;
     // the latent gradient; the two-pass form writes its cell-corner sums over
@@ -1681,7 +1832,7 @@ struct TrainEntry {
                          (const float*)dz, (float*)ws);
       if ((rc = check_launch())) return rc;
       hipLaunchKernelGGL((vertex_sum_kernel<F>), dim3(grid_blocks(nv * (F / 4), 256, device_cus() * 32)), dim3(256), 0,
-                         st, nd.R, sub_log2, (const float*)ws, d_latent);
+                         st, nd.R, sub_log2, (const float*)ws, d_latent, adam_lat);
       if ((rc = check_launch())) return rc;
     } else {
       // lanes per cell: about one per four points of an average cell, at most 8
@@ -1692,15 +1843,19 @@ struct TrainEntry {
                          st, xyz, times, kt, nd.K, nd.R, nd.key_stride, (const int*)off, (const int*)order,
                          (const float*)dz, d_latent, lpc_log2);
       if ((rc = check_launch())) return rc;
+      if (adam_lat.p) {
+        hipLaunchKernelGGL(adam_kernel, dim3(grid_blocks(nv * nd.K * (F / 4), 256, device_cus() * 32)), dim3(256), 0, st,
+                           (const float*)d_latent, nv * nd.K * (F / 4), adam_lat);
+        if ((rc = check_launch())) return rc;
+      }
     }
     const long long nwts = (long long)C * TC::G::K0IN + C + (long long)(H - 1) * (C * C + C) +
                            (long long)nd.NO * (C + 1);
     const float loss_scale = target && n > 0 ? 1.0f / (float)n : 1.0f;
-    hipLaunchKernelGGL((gather_kernel<C, F, L, ACT, TE, FM>), dim3(grid_blocks(nwts + 1, 128, 1024)), dim3(128), 0, st, H,
-                       nd.NO, (const float*)partial, ng, d_weights, out_loss, loss_scale);
-    if ((rc = check_launch())) return rc;
-    hipLaunchKernelGGL((gather_long_kernel<C, F, L, ACT, TE, FM>), dim3((H - 1) * C + nd.NO + 1), dim3(64), 0, st, H,
-                       nd.NO, (const float*)partial, ng, d_weights, out_loss, loss_scale);
+    const int n_short = grid_blocks(nwts, kGatherThreads, 1024), n_long = (H - 1) * C + nd.NO + 1;
+    hipLaunchKernelGGL((gather_kernel<C, F, L, ACT, TE, FM>), dim3(n_short + (n_long * 64 + kGatherThreads - 1) / kGatherThreads),
+                       dim3(kGatherThreads), 0, st, H, nd.NO, (const float*)partial, ng, d_weights, out_loss, loss_scale,
+                       n_short, adam_w);
     return check_launch();
   }
 };
@@ -1774,9 +1929,17 @@ int launch_train(const NetDev& nd, const KeyTimes& kt, float* latent, float* wei
   NetDev net = nd;
   net.weights = weights;
   int rc = 1;
+  AdamDev adam_lat = {}, adam_w = {};
+  if (use_adam) {
+    const double bc1 = 1.0 - pow((double)beta1, (double)step);
+    const double bc2 = 1.0 - pow((double)beta2, (double)step);
+    const float isb2 = (float)(1.0 / sqrt(bc2));
+    adam_lat = {latent, m_lat, v_lat, (float)(lr_grid / bc1), beta1, beta2, isb2, eps};
+    adam_w = {weights, m_w, v_w, (float)(lr_mlp / bc1), beta1, beta2, isb2, eps};
+  }
 #define FV_TRAIN_RUN(C_, F_, L_, ACT_, TE_, FM_)                                                             \
   rc = TrainEntry<C_, F_, L_, ACT_, TE_, FM_>::run(net, kt, latent, d_latent, d_weights, xyz, times, n, target,     \
-                                              target_grad, grad_weight, dloss_dy, out_loss, workspace, half != 0, st)
+                                              target_grad, grad_weight, dloss_dy, out_loss, workspace, half != 0, adam_lat, adam_w, st)
 #define X(C_, F_, L_)                                                        \
   if (nd.C == C_ && nd.F == F_ && nd.L == L_) {                              \
     if (nd.time_enc != 0 || nd.fmat) {                                       \
@@ -1805,20 +1968,7 @@ int launch_train(const NetDev& nd, const KeyTimes& kt, float* latent, float* wei
 #undef X
 #undef FV_TRAIN_RUN
   (void)ws_bytes;
-  if (rc != 0 || !use_adam) return rc;
-  const double bc1 = 1.0 - pow((double)beta1, (double)step);
-  const double bc2 = 1.0 - pow((double)beta2, (double)step);
-  const long long nlat = (long long)nd.K * nd.R * nd.R * nd.R * nd.F;
-  static const int kTimeInputs[4] = {0, 1, 8, 9};
-  const long long nw = (long long)nd.C * (3 + nd.F + 6 * nd.L + kTimeInputs[nd.time_enc]) + nd.C +
-                       (long long)(nd.H - 1) * (nd.C * nd.C + nd.C) + (long long)nd.NO * (nd.C + 1);
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_blocks(nlat, 256, device_cus() * 8)), dim3(256), 0, st, latent, d_latent,
-                     m_lat, v_lat, nlat, (float)(lr_grid / bc1), beta1, beta2, (float)(1.0 / sqrt(bc2)), eps);
-  rc = check_launch();
-  if (rc) return rc;
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_blocks(nw, 256, device_cus() * 8)), dim3(256), 0, st, weights, d_weights,
-                     m_w, v_w, nw, (float)(lr_mlp / bc1), beta1, beta2, (float)(1.0 / sqrt(bc2)), eps);
-  return check_launch();
+  return rc;
 }
 
 }  // namespace fvsrn_detail

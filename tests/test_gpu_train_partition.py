@@ -1,0 +1,117 @@
+"""The training step over the edges of its launches: waves per workgroup and
+partly filled workgroups, register- and slice-resident gradient tiles by layer
+count, the workgroups' sums, the cell scan's two forms, and Adam in the
+gradient kernels or in its own launch. Gradients against the FP64 oracle: within
+1e-4 of the largest in FP32 (sums over thousands of points) and 3e-3 with FP16
+network passes; one Adam update within 1e-6 of the oracle's for the same
+gradients; dW the same bits in every call."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2112_01579_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-4, "f16": 3e-3}
+
+
+@pytest.fixture(scope="module")
+def FV():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2112_01579_amd import fvsrn
+    fvsrn.lib()
+    return fvsrn
+
+
+def _rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-30))
+
+
+def _step(FV, spec, n, prec, key_times=None, seed=61):
+    lat, w = I.net_params(spec, seed)
+    gnet, onet = FV.Network(spec, lat, w, key_times), O.Net(spec, lat, w, key_times)
+    rng = np.random.default_rng(seed + n)
+    xyz = I.uniform_points(n, seed + 1, -0.99, 0.99)
+    times = None
+    d = O.eval_points(onet, xyz)
+    if key_times is not None:
+        times = rng.choice(np.array([-1.0, 0.0, 0.4, 1.0, 1.75, 9.0], np.float32), n)
+        for t in np.unique(times):
+            d[times == t] = O.eval_points(onet, xyz[times == t], float(t))
+    # targets away from the prediction, so that sign(d - t) is the oracle's
+    target = (d + rng.uniform(0.02, 0.3, n) * rng.choice([-1, 1], n)).astype(np.float32)
+    dl_ref, dw_ref, loss_ref = O.train_grads(onet, xyz, target=target.astype(np.float64), times=times)
+    cu = lambda a: None if a is None else torch.from_numpy(a).cuda()  # noqa: E731
+    out = []
+    for _ in range(2):
+        d_lat, d_w, loss = torch.empty_like(gnet.latent), torch.empty_like(gnet.weights), torch.zeros(1, device="cuda")
+        FV.fvsrn_train_step(gnet, d_lat, d_w, cu(xyz), target=cu(target), times=cu(times), out_loss=loss, precision=prec)
+        out.append((d_lat.cpu().numpy(), d_w.cpu().numpy(), loss.item()))
+    assert np.array_equal(out[0][1], out[1][1]) and out[0][2] == out[1][2]
+    e_w, e_l = _rel(out[0][1], dw_ref), _rel(out[0][0], dl_ref)
+    print("train c%d H%d R%d K%d n%d %s: dW %.3g dG %.3g loss %.3g" % (
+        spec.c, spec.H, spec.R, spec.K, n, prec, e_w, e_l, abs(out[0][2] - loss_ref) / loss_ref), flush=True)
+    assert e_w <= TOL[prec] and e_l <= TOL[prec]
+    assert abs(out[0][2] - loss_ref) <= (1e-5 if prec == "f32" else 1e-3) * abs(loss_ref) + 1e-7
+
+
+# 16-point chunks: 1 wave; one more point; 257 waves (65 workgroups of four, the
+# last with one); 1022 (256 of four, the last with two); 1500 (250 of six); 2048
+# and one chunk more (a ninth of a wave's chunks)
+@pytest.mark.parametrize("n", [1, 16, 17, 16 * 257, 16 * 1021 + 5, 16 * 1500, 16 * 2048 + 16])
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+def test_train_wave_counts(FV, n, prec):
+    _step(FV, I.NetSpec(R=8, F=8, L=4, c=32, H=3), n, prec)
+
+
+@pytest.mark.parametrize("c,H", [(32, 1), (32, 2), (32, 4), (32, 8), (48, 1), (48, 2), (48, 8)])
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+def test_train_layer_counts(FV, c, H, prec):
+    _step(FV, I.NetSpec(R=6, F=16, L=8, c=c, H=H), 3001, prec)
+
+
+# 4096 cells (one block of the scan), 4913 (two), 64000 (16, each adding the
+# counts before it) and 68921 (17, summed first)
+@pytest.mark.parametrize("R", [2, 17, 18, 41, 42])
+def test_train_cell_scan(FV, R):
+    _step(FV, I.NetSpec(R=R, F=8, L=4, c=32, H=2), 2999, "f32")
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+@pytest.mark.parametrize("n", [33, 5001])
+def test_train_keyframes(FV, n, prec):
+    _step(FV, I.NetSpec(R=5, F=16, L=8, c=32, H=2, K=3), n, prec, key_times=[0.0, 1.0, 2.5])
+
+
+@pytest.mark.parametrize("K,R", [(1, 9), (1, 30), (3, 6)])
+def test_train_adam_in_gradient_kernels(FV, K, R):
+    """Two-pass latent gradient (K = 1, fits the slices) with Adam in its
+    kernel, one-pass (K = 3) with Adam in a launch of its own; the weights'
+    always in the kernel that writes their gradient. Nonzero moments, step 7."""
+    spec = I.NetSpec(R=R, F=8, L=4, c=32, H=3, K=K)
+    kt = [0.0, 1.0, 2.0] if K > 1 else None
+    lat, w = I.net_params(spec, 71)
+    gnet = FV.Network(spec, lat, w, kt)
+    rng = np.random.default_rng(72)
+    n = 4000
+    xyz, target = I.uniform_points(n, 73), rng.uniform(0.0, 1.0, n).astype(np.float32)
+    times = rng.uniform(0.0, 2.0, n).astype(np.float32) if K > 1 else None
+    mom = {k: (rng.normal(0.0, 1e-4, s) if k[0] == "m" else rng.uniform(1e-9, 1e-8, s)).astype(np.float32)
+           for k, s in (("m_latent", spec.n_latent), ("v_latent", spec.n_latent), ("m_weights", spec.n_weights),
+                        ("v_weights", spec.n_weights))}
+    opt = dict(lr_grid=1e-2, lr_mlp=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, step=7,
+               **{k: torch.from_numpy(v).cuda() for k, v in mom.items()})
+    d_lat, d_w = torch.empty_like(gnet.latent), torch.empty_like(gnet.weights)
+    FV.fvsrn_train_step(gnet, d_lat, d_w, torch.from_numpy(xyz).cuda(), target=torch.from_numpy(target).cuda(), adam=opt,
+                        times=None if times is None else torch.from_numpy(times).cuda())
+    f = lambda x: float(np.float32(x))  # noqa: E731
+    for p0, g, m, v, lr, p in ((lat.reshape(-1), d_lat, "m_latent", "v_latent", 1e-2, gnet.latent),
+                                       (w, d_w, "m_weights", "v_weights", 1e-3, gnet.weights)):
+        p64, m64, v64 = (a.astype(np.float64).copy() for a in (p0, mom[m], mom[v]))
+        O.adam(p64, g.cpu().numpy().astype(np.float64), m64, v64, f(lr), f(0.9), f(0.999), f(1e-8), 7)
+        assert np.abs(p.cpu().numpy() - p64).max() <= 1e-6
+        assert np.abs(opt[m].cpu().numpy() - m64).max() <= 1e-6 * np.abs(m64).max()
+        assert np.abs(opt[v].cpu().numpy() - v64).max() <= 1e-6 * np.abs(v64).max()
