@@ -144,7 +144,7 @@ def _check(status: int, what: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # ctypes converts it (argtypes)
 
 
 def check_tensor(t, name: str, dtype=torch.float32, shape=None, numel=None, device=None):
@@ -152,6 +152,13 @@ def check_tensor(t, name: str, dtype=torch.float32, shape=None, numel=None, devi
     of the given shape (None entries match any size) or element count,
     contiguous, and on a GPU (``device`` when given). Raises
     FvsrnArgumentError before any library call."""
+    # all of it in one expression for the tensors that pass; the steps below
+    # name what is wrong with the others
+    if (isinstance(t, torch.Tensor) and t.dtype == dtype and t.is_cuda and (device is None or t.device == device) and
+            (numel is None or t.numel() == numel) and
+            (shape is None or (len(shape) == t.dim() and all(w is None or w == g for w, g in zip(shape, t.shape)))) and
+            t.is_contiguous()):
+        return t
     if not isinstance(t, torch.Tensor):
         raise FvsrnArgumentError("%s must be a torch tensor, got %s" % (name, type(t).__name__))
     if t.dtype != dtype:
@@ -186,9 +193,10 @@ def _check_points(xyz, dev):
 
 
 def _stream(stream=None):
+    """The handle of ``stream``, or of the current device's current stream."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 # ----------------------------------------------------------- structs

@@ -30,6 +30,7 @@ Workloads (stand-ins for the paper's datasets, which are not available):
 from __future__ import annotations
 
 import dataclasses
+import functools
 import math
 from typing import List, Optional, Sequence, Tuple
 
@@ -73,7 +74,7 @@ class NetSpec:
         shapes = [(self.c, self.K0)] + [(self.c, self.c)] * (self.H - 1) + [(self.outputs, self.c)]
         return shapes
 
-    @property
+    @functools.cached_property
     def n_weights(self) -> int:
         return sum(o * i + o for o, i in self.layer_shapes())
 
