@@ -24,13 +24,23 @@ namespace {
 // differences, the network's predicted gradient, the adjoint (Sec. 6).
 enum { kShadeNone = 0, kShadeFwd = 1, kShadeFD = 2, kShadePred = 3, kShadeAdj = 4 };
 
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int kRayBytes = 9 * 8 * kWave;  // a wave's FP64 rays in LDS (split render)
+
 // FP32 sine networks with the octave features evaluate on the FP16 matrix
-// cores (fvsrn_split.hpp) wherever only values are needed; forward-mode
-// tangents and the adjoint's deltas have no bound that the split could rely
-// on and stay on the FP32 MFMA, as do the other activations.
-template <class CF, int MODE>
+// cores (fvsrn_split.hpp) wherever values are needed, and for the adjoint of up
+// to kSplitAdjLayers layers while its two sets of weight fragments leave LDS
+// for at least a wave per SIMD (c = 48: up to H = 3, with F = 16 up to 2; with 5
+// waves, c = 48, F = 8, H = 3 takes 197 us for 10^6 gradients against 276 on the
+// FP32 MFMA, H = 4 would run on 2). Forward-mode tangents, the other adjoints
+// and the other activations stay on the FP32 MFMA.
+template <class CF, int MODE, int HH = 0>
 constexpr bool use_split() {
-  return CF::P == kF32 && CF::ACT == kSine && CF::TE == 0 && !CF::FM && MODE != kShadeFwd && MODE != kShadeAdj;
+  return CF::P == kF32 && CF::ACT == kSine && CF::TE == 0 && !CF::FM && MODE != kShadeFwd &&
+         (MODE != kShadeAdj || (HH > 0 && HH <= kSplitAdjLayers &&
+                                SplitGeo<CF>::weight_bytes(HH) + SplitAdjGeo<CF>::back_bytes(HH) +
+                                        4 * (SplitGeo<CF>::WAVE_BYTES + kRayBytes + SplitAdjGeo<CF>::GRAD_BYTES) <=
+                                    kLdsBytes));
 }
 
 // Waves per workgroup cap (sets the VGPR budget through the launch bounds):
@@ -46,11 +56,11 @@ constexpr bool use_split() {
 // derivatives of two N-tiles in registers: 3 waves per SIMD for the c = 32
 // FP16 network on a packed grid (151 -> 138 ms on the study views), 2
 // otherwise (c = 48 measured 47 -> 48 ms at 3).
-// FP32 networks add the FP64 ray of their sample positions (about 10
-// registers).
-template <class CF, int MODE, bool POINTS = false>
+// FP32 networks off the split path add the FP64 ray of their sample positions
+// (about 10 registers).
+template <class CF, int MODE, bool POINTS = false, int HH = 0>
 constexpr int max_waves() {
-  if (use_split<CF, MODE>()) return 12;
+  if (use_split<CF, MODE, HH>()) return MODE == kShadeAdj ? 8 : 12;
   if (MODE == kShadeAdj) return (CF::P == kF16 && CF::C == 32 && CF::G16) ? 12 : 8;
   if (MODE == kShadeFwd) return (CF::P == kF16 && CF::C <= 48 && CF::G16) ? 12 : 8;
   if (MODE == kShadeFD) {
@@ -75,23 +85,23 @@ struct TileShape {
   __host__ __device__ static constexpr int log_w(int sh) { return (7 - LOG_LPR - sh) / 2; }
   __host__ __device__ static constexpr int log_h(int sh) { return (6 - LOG_LPR - sh) / 2; }
 };
-constexpr int kLdsBytes = 160 * 1024;
-
 // LDS bytes of a workgroup besides its waves' input tiles: the forward weight
 // fragments, and for the adjoint the transposed ones.
-template <class CF, int MODE>
+template <class CF, int MODE, int HH = 0>
 __host__ __device__ int fixed_lds_bytes(int H) {
   using G = typename CF::G;
-  if constexpr (use_split<CF, MODE>()) return SplitGeo<CF>::weight_bytes(H);
+  if constexpr (use_split<CF, MODE, HH>())
+    return SplitGeo<CF>::weight_bytes(H) + (MODE == kShadeAdj ? SplitAdjGeo<CF>::back_bytes(H) : 0);
   else return G::weight_bytes(H) + (MODE == kShadeAdj ? G::back_bytes(H) : 0);
 }
 
 // LDS bytes of one wave's input tile; the split render also keeps its lanes'
 // FP64 rays there, which would cost 18 registers over the MLP.
-constexpr int kRayBytes = 9 * 8 * kWave;
-template <class CF, int MODE, bool POINTS = false>
+template <class CF, int MODE, bool POINTS = false, int HH = 0>
 constexpr int wave_lds_bytes() {
-  if constexpr (use_split<CF, MODE>()) return SplitGeo<CF>::WAVE_BYTES + (POINTS ? 0 : kRayBytes);
+  if constexpr (use_split<CF, MODE, HH>())
+    return SplitGeo<CF>::WAVE_BYTES + (POINTS ? 0 : kRayBytes) +
+           (MODE == kShadeAdj ? SplitAdjGeo<CF>::GRAD_BYTES : 0);
   else return CF::G::FEAT_BYTES;
 }
 
@@ -101,9 +111,9 @@ constexpr int wave_lds_bytes() {
 // ceil(w / 4) of the first SIMD's wave slots: two workgroups of 6 waves do
 // not fit where one of 12 does (measured: the second one waited for the
 // first, 24.7 against 18.8 ms for a 1024^2 view of the FP32 study network).
-template <class CF, int MODE, bool POINTS = false>
+template <class CF, int MODE, bool POINTS = false, int HH = 0>
 int blocks_per_cu(int wpb, size_t shm) {
-  const int by_lds = (int)(kLdsBytes / shm), by_regs = max_waves<CF, MODE, POINTS>() / 4 / ((wpb + 3) / 4);
+  const int by_lds = (int)(kLdsBytes / shm), by_regs = max_waves<CF, MODE, POINTS, HH>() / 4 / ((wpb + 3) / 4);
   return by_lds < by_regs ? by_lds : by_regs;
 }
 
@@ -113,13 +123,14 @@ int blocks_per_cu(int wpb, size_t shm) {
 // sizes that reach it, the smallest: several smaller workgroups per CU let
 // the dispatcher replace a finished one while another still runs its long
 // rays (measured: 3 x 4 waves beat 1 x 12 waves by 12% on the BF16 path).
-template <class CF, int MODE, bool POINTS = false>
+template <class CF, int MODE, bool POINTS = false, int HH = 0>
 int waves_per_block(int H) {
-  constexpr int cap = max_waves<CF, MODE, POINTS>();
-  const int wb = fixed_lds_bytes<CF, MODE>(H);
+  constexpr int cap = max_waves<CF, MODE, POINTS, HH>();
+  const int wb = fixed_lds_bytes<CF, MODE, HH>(H);
   int best = 0, best_waves = 0;
   for (int w = 1; w <= cap; ++w) {
-    const int waves = w * blocks_per_cu<CF, MODE, POINTS>(w, (size_t)wb + w * wave_lds_bytes<CF, MODE, POINTS>());
+    const int waves =
+        w * blocks_per_cu<CF, MODE, POINTS, HH>(w, (size_t)wb + w * wave_lds_bytes<CF, MODE, POINTS, HH>());
     if (waves > best_waves) {
       best = w;
       best_waves = waves;
@@ -129,9 +140,9 @@ int waves_per_block(int H) {
 }
 
 // Workgroups that the GPU holds at once.
-template <class CF, int MODE, bool POINTS = false>
+template <class CF, int MODE, bool POINTS = false, int HH = 0>
 long long resident_blocks(int wpb, size_t shm) {
-  return (long long)device_cus() * blocks_per_cu<CF, MODE, POINTS>(wpb, shm);
+  return (long long)device_cus() * blocks_per_cu<CF, MODE, POINTS, HH>(wpb, shm);
 }
 
 // ----------------------------------------------------- TF, camera, march
@@ -208,7 +219,7 @@ __device__ inline void composite(Accum& acc, const float rgba[4], float len) {
 // unshaded and forward-mode kernels 3% where it does not run; the adjoint is
 // compiled with it alone).
 template <class CF, int MODE, int HH = 0, bool SEG = MODE == kShadeAdj>
-__global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(NetDev nd, TFDev tf, ViewBatch vb,
+__global__ __launch_bounds__((max_waves<CF, MODE, false, HH>() * 64)) void march_kernel(NetDev nd, TFDev tf, ViewBatch vb,
                                                                                   MarchDev m, float* out,
                                                                                   unsigned long long* stats,
                                                                                   unsigned int* queue,
@@ -221,11 +232,13 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
   constexpr int LPR = TileShape<MODE>::LPR;
   constexpr bool ADJ = MODE == kShadeAdj;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr bool SPLIT = use_split<CF, MODE>();
+  constexpr bool SPLIT = use_split<CF, MODE, HH>();
   if constexpr (SPLIT) stage_split<CF>(nd, smem);
   else stage_weights<CF>(nd, smem);
-  char* bsm = smem + G::weight_bytes(nd.H);  // transposed fragments (adjoint)
-  if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
+  // transposed fragments (adjoint)
+  char* bsm = smem + (SPLIT ? SplitGeo<CF>::weight_bytes(nd.H) : G::weight_bytes(nd.H));
+  if constexpr (ADJ && SPLIT) stage_split_adj<CF>(nd, bsm);
+  else if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
   __syncthreads();
   // the wave index is wave-uniform; saying so keeps the tile, its camera and
   // the latent grid's buffer resource in scalar registers
@@ -246,11 +259,12 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
                            FD && (q == 5 || q == 6) ? fh : 0.0f};
   const float inv_2h = FD ? 0.5f / m.fd_step : 0.0f;
   const bool fixed = m.fixed_steps > 0;
-  char* wlds = smem + fixed_lds_bytes<CF, MODE>(nd.H) + wave * wave_lds_bytes<CF, MODE>();
+  char* wlds = smem + fixed_lds_bytes<CF, MODE, HH>(nd.H) + wave * wave_lds_bytes<CF, MODE, false, HH>();
   E* feat = reinterpret_cast<E*>(wlds);
   E* myrow = feat + lane * G::ROW;
   SplitTile st = {reinterpret_cast<f4*>(wlds), reinterpret_cast<f4*>(wlds) + kWave};
   double* lray = reinterpret_cast<double*>(wlds + 2 * kWave * sizeof(f4)) + lane;  // SPLIT: this lane's ray
+  f4* lgrad = reinterpret_cast<f4*>(wlds + 2 * kWave * sizeof(f4) + kRayBytes);    // and the partial gradients
   unsigned long long n_samp = 0, n_hit = 0, iters = 0;
   for (int tile = next_tile(queue, lane); tile < n_tiles; tile = next_tile(queue, lane)) {
     const int v = tile / tiles_per_view;
@@ -325,7 +339,14 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
       wave_lds_sync();
       f4 yo;
       float ga[3] = {0.0f, 0.0f, 0.0f};
-      if constexpr (ADJ) {
+      if constexpr (ADJ && SPLIT) {
+        yo[0] = mlp_split_adj<CF, HH>(smem, bsm, st, lgrad, ls);
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int a = 0; a < 3; ++a) ga[a] += lgrad[4 * lane + k][a];
+      } else if constexpr (ADJ) {
         // the network and its adjoint; each row then holds dy/d(input row)
         yo[0] = mlp_tile_adj<CF, HH>(smem, bsm, feat);
         wave_lds_sync();
@@ -442,7 +463,7 @@ __global__ __launch_bounds__((max_waves<CF, MODE>() * 64)) void march_kernel(Net
 // and forward-mode gradient; kShadeAdj -- density and adjoint gradient (HH:
 // layer count, as for the render kernel).
 template <class CF, int PM, int HH = 0>
-__global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kernel(NetDev nd, const float* xyz, long long n,
+__global__ __launch_bounds__((max_waves<CF, PM, true, HH>() * 64)) void points_kernel(NetDev nd, const float* xyz, long long n,
                                                                             int key, float key_w, float* out_d,
                                                                             float* out_g) {
   using G = typename CF::G;
@@ -451,14 +472,15 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
   constexpr bool ADJ = PM == kShadeAdj;
   constexpr int PER = GRAD ? 16 : 64;  // points per wave step
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr bool SPLIT = use_split<CF, PM>();
+  constexpr bool SPLIT = use_split<CF, PM, HH>();
   if constexpr (SPLIT) stage_split<CF>(nd, smem);
   else stage_weights<CF>(nd, smem);
-  char* bsm = smem + G::weight_bytes(nd.H);
-  if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
+  char* bsm = smem + (SPLIT ? SplitGeo<CF>::weight_bytes(nd.H) : G::weight_bytes(nd.H));
+  if constexpr (ADJ && SPLIT) stage_split_adj<CF>(nd, bsm);
+  else if constexpr (ADJ) stage_backward_adj<CF>(nd, bsm);
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  char* wlds = smem + fixed_lds_bytes<CF, PM>(nd.H) + wave * wave_lds_bytes<CF, PM, true>();
+  char* wlds = smem + fixed_lds_bytes<CF, PM, HH>(nd.H) + wave * wave_lds_bytes<CF, PM, true, HH>();
   E* feat = reinterpret_cast<E*>(wlds);
   E* myrow = feat + lane * G::ROW;
   SplitTile st = {reinterpret_cast<f4*>(wlds), reinterpret_cast<f4*>(wlds) + kWave};
@@ -493,10 +515,20 @@ __global__ __launch_bounds__((max_waves<CF, PM, true>() * 64)) void points_kerne
     wave_lds_sync();
     load_pos(c + stride);
     if constexpr (ADJ) {
-      const float o = mlp_tile_adj<CF, HH>(smem, bsm, feat);
-      wave_lds_sync();
-      float ga[3] = {0.0f, 0.0f, 0.0f};
-      input_vjp<CF>(myrow, ls, x, y, z, ga);
+      float o, ga[3] = {0.0f, 0.0f, 0.0f};
+      if constexpr (SPLIT) {
+        f4* lgrad = reinterpret_cast<f4*>(wlds + 2 * kWave * sizeof(f4));
+        o = mlp_split_adj<CF, HH>(smem, bsm, st, lgrad, ls);
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int a = 0; a < 3; ++a) ga[a] += lgrad[4 * lane + k][a];
+      } else {
+        o = mlp_tile_adj<CF, HH>(smem, bsm, feat);
+        wave_lds_sync();
+        input_vjp<CF>(myrow, ls, x, y, z, ga);
+      }
       wave_lds_sync();
       const float d = sigmoid_f(o), sg = d * (1.0f - d);
       if (ok) {
@@ -575,11 +607,12 @@ void launch_march(long long blocks, int wpb, size_t shm, const NetDev& nd, const
 template <class CF, int MODE, int HH = 0>
 int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, const MarchDev& m, float* out,
                     unsigned long long* stats, hipStream_t st) {
-  const int wpb = waves_per_block<CF, MODE>(nd.H);
+  const int wpb = waves_per_block<CF, MODE, false, HH>(nd.H);
   if (wpb < 1) return kLaunchNoLds;
-  const size_t shm = (size_t)fixed_lds_bytes<CF, MODE>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, MODE>();
+  const size_t shm =
+      (size_t)fixed_lds_bytes<CF, MODE, HH>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, MODE, false, HH>();
   // the workgroups the CUs hold at once, fewer for small launches
-  const long long resident = resident_blocks<CF, MODE>(wpb, shm);
+  const long long resident = resident_blocks<CF, MODE, false, HH>(wpb, shm);
   const int sh = segments_log2<MODE>(vb, m, resident * wpb);
   const int tw = 1 << TileShape<MODE>::log_w(sh), th = 1 << TileShape<MODE>::log_h(sh);
   const int tx = (vb.width + tw - 1) / tw, ty = (vb.height + th - 1) / th;
@@ -601,9 +634,9 @@ template <class CF, int PM, int HH = 0>
 int launch_points_t(const NetDev& nd, const float* xyz, long long n, int key, float key_w, float* out_d,
                     float* out_g, hipStream_t st) {
   constexpr int PER = PM == kShadeFwd ? 16 : 64;
-  const int wpb = waves_per_block<CF, PM, true>(nd.H);
+  const int wpb = waves_per_block<CF, PM, true, HH>(nd.H);
   if (wpb < 1) return kLaunchNoLds;
-  const size_t shm = (size_t)fixed_lds_bytes<CF, PM>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, PM, true>();
+  const size_t shm = (size_t)fixed_lds_bytes<CF, PM, HH>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, PM, true, HH>();
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)points_kernel<CF, PM, HH>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -613,7 +646,7 @@ int launch_points_t(const NetDev& nd, const float* xyz, long long n, int key, fl
   // persistent: the workgroups the GPU holds at once walk the chunks (equal
   // cost), so the weights are staged once per workgroup and no workgroup
   // waits for another to release its LDS
-  const int blocks = grid_blocks((n + PER - 1) / PER, wpb, (int)resident_blocks<CF, PM, true>(wpb, shm));
+  const int blocks = grid_blocks((n + PER - 1) / PER, wpb, (int)resident_blocks<CF, PM, true, HH>(wpb, shm));
   hipLaunchKernelGGL((points_kernel<CF, PM, HH>), dim3(blocks), dim3(wpb * 64), shm, st, nd, xyz, n, key, key_w,
                      out_d, out_g);
   return check_launch();

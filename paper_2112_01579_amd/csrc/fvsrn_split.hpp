@@ -50,7 +50,7 @@ struct SplitGeo {
   static constexpr int HID = WH + 2 * C * 4;              // fragments, row scales, biases
   static constexpr int WO = 4 * HS * FRAG;
   static constexpr int OUT = WO + 32;                     // fragments, row scales, biases
-  __host__ __device__ static int weight_bytes(int H) { return L0 + (H - 1) * HID + OUT; }
+  __host__ __device__ static constexpr int weight_bytes(int H) { return L0 + (H - 1) * HID + OUT; }
   static constexpr int WAVE_BYTES = 2 * kWave * 16;       // position and cell of a wave's samples
 };
 
@@ -234,6 +234,26 @@ struct QuarterGather {
     }
   }
 
+  // d[c] = u . corner c (a uint8 grid's offsets drop out of the derivative)
+  __device__ inline void dot(const float* u, int g, const float* dq, float d[8]) const {
+    float us[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) us[j] = D == kU8 ? u[j] * dq[2 * (Q * g + j) + 1] : u[j];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      d[c] = 0.0f;
+#pragma unroll
+      for (int j = 0; j < Q; ++j) d[c] = fmaf(us[j], value(c, j), d[c]);
+    }
+  }
+
+  // channel j of corner c (a code of a uint8 grid)
+  __device__ inline float value(int c, int j) const {
+    if constexpr (D == kU8) return (float)((raw[c][0] >> (8 * j)) & 0xffu);
+    else if constexpr (D == kF16) return (float)__builtin_bit_cast(h2, raw[c][j / 2])[j % 2];
+    else return __uint_as_float(raw[c][j]);
+  }
+
   // z += sum over corners of w * corner
   __device__ inline void add(const float w[8], int g, const float* dq, float* z) const {
     if constexpr (D == kU8) {
@@ -241,7 +261,7 @@ struct QuarterGather {
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
 #pragma unroll
-        for (int j = 0; j < Q; ++j) acc[j] = fmaf(w[c], (float)((raw[c][0] >> (8 * j)) & 0xffu), acc[j]);
+        for (int j = 0; j < Q; ++j) acc[j] = fmaf(w[c], value(c, j), acc[j]);
         wsum += w[c];
       }
       const float* d = dq + 2 * Q * g;
@@ -251,12 +271,7 @@ struct QuarterGather {
 #pragma unroll
       for (int c = 0; c < 8; ++c)
 #pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          float v;
-          if constexpr (D == kF16) v = (float)__builtin_bit_cast(h2, raw[c][j / 2])[j % 2];
-          else v = __uint_as_float(raw[c][j]);
-          z[j] = fmaf(w[c], v, z[j]);
-        }
+        for (int j = 0; j < Q; ++j) z[j] = fmaf(w[c], value(c, j), z[j]);
     }
   }
 };
@@ -340,118 +355,136 @@ __device__ inline void split_inputs(const SplitTile& st, const LatentSrc& ls, in
   }
 }
 
-// The network on the wave's 64 samples; returns the output pre-activations of
-// this lane's own sample.
+// A pair of N-tiles on its way through the network: the B operands (hi, lo) and
+// the accumulators.
 template <class CF>
-__device__ inline f4 mlp_split(const char* wsm, const SplitTile& st, const LatentSrc& ls, int H) {
+struct SplitPair {
   using SG = SplitGeo<CF>;
   using P16 = PrecT<kF16>;
   using P32 = PrecT<kF32>;
-  constexpr int C = SG::C, MT = SG::MT, HS = SG::HS, S0 = SG::S0, Q = SG::Q, NT = 2;
-  const int lane = threadIdx.x & 63;
-  const int g = lane >> 4;
-  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  const h8* W0 = reinterpret_cast<const h8*>(wsm);
-  const float* WL = reinterpret_cast<const float*>(wsm + SG::W0F);
-  const f4* U0 = reinterpret_cast<const f4*>(wsm + SG::W0F + SG::W0L);
-  constexpr int NS = HS > S0 ? HS : S0;
-  f4 out[NT];
+  static constexpr int MT = SG::MT, HS = SG::HS, S0 = SG::S0, Q = SG::Q, NT = 2, NS = HS > S0 ? HS : S0;
+  f4 acc[NT][MT], lin[NT][MT];  // row-scaled; layer 0: latent, position and bias
+  h8 bh[NT][NS], bl[NT][NS];
+
+  // hi hi + hi lo + lo hi of one K32 step
+  __device__ inline void mma3(const h8* frag, int s, f4 c[NT]) const {
+    const int lane = threadIdx.x & 63;
+    const h8 ah = frag[lane], al = frag[kWave + lane];
 #pragma unroll
-  for (int u = 0; u < NT; ++u) out[u] = zero;
-  for (int tp = 0; tp < 4; tp += NT) {
-    f4 acc[NT][MT], lin[NT][MT];  // Fourier part (row-scaled); latent, position and bias
-    h8 bh[NT][NS], bl[NT][NS];
-    {
-      float z[NT][Q], tail[NT];
-      if (ls.dtype == kF32) split_inputs<CF, kF32, NT, NS>(st, ls, tp, bh, bl, z, tail);
-      else if (ls.dtype == kF16) split_inputs<CF, kF16, NT, NS>(st, ls, tp, bh, bl, z, tail);
-      else split_inputs<CF, kU8, NT, NS>(st, ls, tp, bh, bl, z, tail);
+    for (int u = 0; u < NT; ++u) c[u] = P16::mma(al, bh[u][s], c[u]);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const float* wl = WL + mt * (Q + 1) * kWave + lane;
+    for (int u = 0; u < NT; ++u) c[u] = P16::mma(ah, bl[u][s], c[u]);
 #pragma unroll
-        for (int u = 0; u < NT; ++u) lin[u][mt] = P32::mma(wl[Q * kWave], tail[u], zero);
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-          for (int u = 0; u < NT; ++u) lin[u][mt] = P32::mma(wl[q * kWave], z[u][q], lin[u][mt]);
-      }
-    }
-    // hi hi + hi lo + lo hi of one K32 step
-    auto mma3 = [&](const h8* frag, int s, f4 c[NT]) {
-      const h8 ah = frag[lane], al = frag[kWave + lane];
-#pragma unroll
-      for (int u = 0; u < NT; ++u) c[u] = P16::mma(al, bh[u][s], c[u]);
-#pragma unroll
-      for (int u = 0; u < NT; ++u) c[u] = P16::mma(ah, bl[u][s], c[u]);
-#pragma unroll
-      for (int u = 0; u < NT; ++u) c[u] = P16::mma(ah, bh[u][s], c[u]);
-    };
+    for (int u = 0; u < NT; ++u) c[u] = P16::mma(ah, bh[u][s], c[u]);
+  }
+
+  template <int STEPS>
+  __device__ inline void product(const h8* frags) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       f4 c[NT];
 #pragma unroll
-      for (int u = 0; u < NT; ++u) c[u] = zero;
+      for (int u = 0; u < NT; ++u) c[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int s = 0; s < S0; ++s) mma3(W0 + (mt * S0 + s) * 2 * kWave, s, c);
+      for (int s = 0; s < STEPS; ++s) mma3(frags + (mt * STEPS + s) * 2 * kWave, s, c);
 #pragma unroll
       for (int u = 0; u < NT; ++u) acc[u][mt] = c[u];
     }
-    // the next B operands: sin of the layer's pre-activations (revolutions)
-    auto pack = [&](const f4* unscale, auto add) {
+  }
+
+  // layer 0 of N-tiles tp, tp + 1: inputs and products
+  __device__ inline void layer0(const char* wsm, const SplitTile& st, const LatentSrc& ls, int tp) {
+    const int lane = threadIdx.x & 63;
+    const float* WL = reinterpret_cast<const float*>(wsm + SG::W0F);
+    float z[NT][Q], tail[NT];
+    if (ls.dtype == kF32) split_inputs<CF, kF32, NT, NS>(st, ls, tp, bh, bl, z, tail);
+    else if (ls.dtype == kF16) split_inputs<CF, kF16, NT, NS>(st, ls, tp, bh, bl, z, tail);
+    else split_inputs<CF, kU8, NT, NS>(st, ls, tp, bh, bl, z, tail);
 #pragma unroll
-      for (int u = 0; u < NT; ++u) {
+    for (int mt = 0; mt < MT; ++mt) {
+      const float* wl = WL + mt * (Q + 1) * kWave + lane;
 #pragma unroll
-        for (int s = 0; s < HS; ++s) {
-          bh[u][s] = bl[u][s] = h8{};
+      for (int u = 0; u < NT; ++u) lin[u][mt] = P32::mma(wl[Q * kWave], tail[u], f4{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            const int mt = 2 * s + v;
-            if (mt >= MT) continue;
-            const f4 us = unscale[4 * mt + g], ad = add(u, mt);
+      for (int q = 0; q < Q; ++q)
 #pragma unroll
-            for (int j = 0; j < 4; j += 2) {
-              h2 hi, lo;
-              split2(sin_rev(fmaf(acc[u][mt][j], us[j], ad[j])), sin_rev(fmaf(acc[u][mt][j + 1], us[j + 1], ad[j + 1])),
-                     hi, lo);
-              bh[u][s][4 * v + j] = hi[0];
-              bh[u][s][4 * v + j + 1] = hi[1];
-              bl[u][s][4 * v + j] = lo[0];
-              bl[u][s][4 * v + j + 1] = lo[1];
+        for (int u = 0; u < NT; ++u) lin[u][mt] = P32::mma(wl[q * kWave], z[u][q], lin[u][mt]);
+    }
+    product<S0>(reinterpret_cast<const h8*>(wsm));
+  }
+
+  __device__ inline void hidden(const char* p) { product<HS>(reinterpret_cast<const h8*>(p)); }
+
+  // The next B operands: sin of the layer's pre-activations (revolutions), row
+  // scales (then biases) at `us`; with DER also act' (cos) into der.
+  template <bool DER>
+  __device__ inline void pack(const f4* us, bool first, f4 (*der)[MT]) {
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+#pragma unroll
+      for (int s = 0; s < HS; ++s) {
+        bh[u][s] = bl[u][s] = h8{};
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          const int mt = 2 * s + v;
+          if (mt >= MT) continue;
+          const f4 sc = us[4 * mt + g], ad = first ? lin[u][mt] : us[SG::C / 4 + 4 * mt + g];
+#pragma unroll
+          for (int j = 0; j < 4; j += 2) {
+            const float r0 = fmaf(acc[u][mt][j], sc[j], ad[j]), r1 = fmaf(acc[u][mt][j + 1], sc[j + 1], ad[j + 1]);
+            h2 hi, lo;
+            split2(sin_rev(r0), sin_rev(r1), hi, lo);
+            if constexpr (DER) {
+              der[u][mt][j] = cos_rev(r0);
+              der[u][mt][j + 1] = cos_rev(r1);
             }
+            bh[u][s][4 * v + j] = hi[0];
+            bh[u][s][4 * v + j + 1] = hi[1];
+            bl[u][s][4 * v + j] = lo[0];
+            bl[u][s][4 * v + j + 1] = lo[1];
           }
         }
       }
-    };
-    pack(U0, [&](int u, int mt) { return lin[u][mt]; });
-    const char* p = wsm + SG::L0;
-    for (int i = 1; i < H; ++i) {
-      const h8* WH = reinterpret_cast<const h8*>(p);
-      const f4* SB = reinterpret_cast<const f4*>(p + SG::WH);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        f4 c[NT];
-#pragma unroll
-        for (int u = 0; u < NT; ++u) c[u] = zero;
-#pragma unroll
-        for (int s = 0; s < HS; ++s) mma3(WH + (mt * HS + s) * 2 * kWave, s, c);
-#pragma unroll
-        for (int u = 0; u < NT; ++u) acc[u][mt] = c[u];
-      }
-      pack(SB, [&](int, int mt) { return SB[C / 4 + 4 * mt + g]; });
-      p += SG::HID;
     }
-    const h8* WO = reinterpret_cast<const h8*>(p);
+  }
+
+  // the output layer at p, into out
+  __device__ inline void output(const char* p, int tp, f4 out[NT]) const {
+    const h8* WO = reinterpret_cast<const h8*>(p) + (threadIdx.x & 63);
 #pragma unroll
     for (int s = 0; s < HS; ++s)
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
-        const h8* frag = WO + ((tp + u) * HS + s) * 2 * kWave + lane;
+        const h8* frag = WO + ((tp + u) * HS + s) * 2 * kWave;
         const h8 ah = frag[0], al = frag[kWave];
         out[u] = P16::mma(al, bh[u][s], out[u]);
         out[u] = P16::mma(ah, bl[u][s], out[u]);
         out[u] = P16::mma(ah, bh[u][s], out[u]);
       }
+  }
+};
+
+// The network on the wave's 64 samples; returns the output pre-activations of
+// this lane's own sample.
+template <class CF>
+__device__ inline f4 mlp_split(const char* wsm, const SplitTile& st, const LatentSrc& ls, int H) {
+  using SG = SplitGeo<CF>;
+  constexpr int NT = 2;
+  f4 out[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) out[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int tp = 0; tp < 4; tp += NT) {
+    SplitPair<CF> sp;
+    sp.layer0(wsm, st, ls, tp);
+    sp.template pack<false>(reinterpret_cast<const f4*>(wsm + SG::W0F + SG::W0L), true, nullptr);
+    const char* p = wsm + SG::L0;
+    for (int i = 1; i < H; ++i) {
+      sp.hidden(p);
+      sp.template pack<false>(reinterpret_cast<const f4*>(p + SG::WH), false, nullptr);
+      p += SG::HID;
+    }
+    sp.output(p, tp, out);
   }
   const f4* so = reinterpret_cast<const f4*>(wsm + SG::L0 + (H - 1) * SG::HID + SG::WO);
   const f4 us = so[0], bo = so[1];
@@ -459,6 +492,270 @@ __device__ inline f4 mlp_split(const char* wsm, const SplitTile& st, const Laten
 #pragma unroll
   for (int j = 0; j < 4; ++j) y[j] = fmaf(y[j], us[j], bo[j]);
   return y;
+}
+
+// ------------------------------------------------------------- adjoint
+//
+// Reverse-mode gradient of an FP32 sine network of up to kSplitAdjLayers
+// layers (Sec. 6). The forward pass is mlp_split's, keeping every layer's act'
+// in registers. The deltas have no bound, so the backward products take three
+// BF16 values per operand (x = b0 + b1 + b2 to 27 bits, any exponent) and the
+// six largest of their products: 6/16 of the FP32 MFMA's cycles. W_0^T's rows
+// are ordered so that lane 16 g + n receives the derivatives of the inputs that it
+// built (its Fourier features, its latent channels, the position's component
+// g) and contracts them with the inputs' Jacobian itself; the four partial
+// gradients of a sample meet in LDS. Measured, FP32 MFMA and here: gradients at 10^6
+// points of the study network 324 -> 161 us (65,537 points 38 -> 28, of which
+// 20 are the weights' way into LDS), at c = 48, F = 16, H = 2 416 -> 215, an 800 x 600
+// Phong view of the study network 34.4 -> 16.5 ms; bound by the VALU
+// (sines, splits) and by 8 waves per CU. The gradients are closer to FP64
+// than before (3.2e-7 of the norm, FP32 MFMA 4.3e-7).
+// Above four layers the derivatives do not fit in registers.
+constexpr int kSplitAdjLayers = 4;
+
+template <class CF>
+struct SplitAdjGeo {
+  using SG = SplitGeo<CF>;
+  static constexpr int SLOTS = SG::NF + SG::Q + 1;  // inputs per lane group: features, channels, one of x y z
+  static constexpr int MB = (SLOTS + 3) / 4;        // M-tiles of W_0^T: slot 4 m + j of group g in row 4 g + j
+  static constexpr int FRAG = 3 * kWave * 16;       // b0, b1, b2
+  static constexpr int WB = SG::MT * SG::HS * FRAG;
+  static constexpr int WB0 = MB * SG::HS * FRAG;
+  __host__ __device__ static constexpr int back_bytes(int H) { return (H - 1) * WB + WB0 + SG::C * 4; }
+  static constexpr int GRAD_BYTES = 4 * kWave * 16;  // a wave's partial gradients [sample][group]
+};
+
+// b0 + b1 + b2 of eight values.
+__device__ inline void split3(const float v[8], b8& b0, b8& b1, b8& b2) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    b0[j] = (__bf16)v[j];
+    const float r = v[j] - (float)b0[j];
+    b1[j] = (__bf16)r;
+    b2[j] = (__bf16)(r - (float)b1[j]);
+  }
+}
+
+template <class CF>
+__device__ void stage_split_adj(const NetDev& nd, char* p) {
+  using SG = SplitGeo<CF>;
+  using SA = SplitAdjGeo<CF>;
+  constexpr int C = SG::C, F = SG::F, L = SG::L, MT = SG::MT, HS = SG::HS, Q = SG::Q;
+  constexpr int K0 = 3 + F + 6 * L;
+  const int H = nd.H;
+  const float* w = nd.weights;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  // a fragment's lane: rows r, K slots of step s; value(row, output channel)
+  auto stage = [&](char* base, int mtiles, auto value) {
+    for (int e = tid; e < mtiles * HS * kWave; e += nt) {
+      const int lane = e & 63, s = (e >> 6) % HS, m = (e >> 6) / HS;
+      const int g = lane >> 4;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ch = 32 * s + (j < 4 ? 4 * g + j : 16 + 4 * g + (j - 4));
+        v[j] = ch < C ? value(m, lane & 15, ch) : 0.0f;
+      }
+      b8 b0, b1, b2;
+      split3(v, b0, b1, b2);
+      b8* f = reinterpret_cast<b8*>(base + (e >> 6) * SA::FRAG) + lane;
+      f[0] = b0;
+      f[kWave] = b1;
+      f[2 * kWave] = b2;
+    }
+  };
+  for (int i = 1; i < H; ++i) {
+    const float* Wi = w + (long long)C * K0 + C + (long long)(i - 1) * (C * C + C);
+    stage(p + (i - 1) * SA::WB, MT, [&](int m, int r, int ch) { return Wi[ch * C + 16 * m + r]; });
+  }
+  p += (H - 1) * SA::WB;
+  stage(p, SA::MB, [&](int m, int r, int ch) {
+    const int g = r >> 2, slot = 4 * m + (r & 3);
+    int col;  // column of W_0
+    if (slot < SG::NF) {
+      const int k = g * SG::OCT + slot / 6, a = slot % 6;
+      col = 3 + F + (a < 3 ? 3 * k + a : 3 * L + 3 * k + (a - 3));
+    } else if (slot < SG::NF + Q) {
+      col = 3 + Q * g + (slot - SG::NF);
+    } else {
+      col = slot == SG::NF + Q && g < 3 ? g : -1;
+    }
+    return col < 0 ? 0.0f : w[(long long)ch * K0 + col];
+  });
+  float* wo = reinterpret_cast<float*>(p + SA::WB0);
+  const float* Wo = w + (long long)C * K0 + C + (long long)(H - 1) * (C * C + C);
+  for (int e = tid; e < C; e += nt) wo[e] = Wo[e];
+}
+
+// The latent channels' share of a sample's gradient, this lane's quarter gq of
+// the channels: ul = dy/d(channel). The trilinear weights are differentiated
+// per axis, zero outside the domain.
+template <class CF, int D>
+__device__ inline void split_latent_vjp(const SplitTile& st, const LatentSrc& ls, int s, int gq, const float* ul,
+                                        float t[3]) {
+  constexpr int F = CF::F, Q = F / 4;
+  const unsigned R = (unsigned)ls.R;
+  unsigned off[8];
+  corner_offsets((unsigned)F, R * F, R * R * F, off);
+  const f4 cf = st.cell[s], p = st.pos[s];
+  const float scale = 0.5f * (float)(ls.R - 1);
+  float d3[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) d3[a] = (p[a] < -1.0f || p[a] > 1.0f) ? 0.0f : scale;
+  const float X[2] = {1.0f - cf[1], cf[1]}, Y[2] = {1.0f - cf[2], cf[2]}, Z[2] = {1.0f - cf[3], cf[3]};
+  t[0] = t[1] = t[2] = 0.0f;
+#pragma unroll
+  for (int key = 0; key < 2; ++key) {
+    if (key == 1 && !ls.g1) break;
+    QuarterGather<F, D> qg;
+    qg.load(key == 0 ? ls.g0 : ls.g1, ls, gq, __float_as_uint(cf[0]), off);
+    float d[8];
+    qg.dot(ul, gq, key == 0 ? ls.dq0 : ls.dq1, d);
+    float v[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int lo = i & 1, hi = i >> 1;
+      v[0] = fmaf(Y[lo] * Z[hi], d[1 + 2 * lo + 4 * hi] - d[2 * lo + 4 * hi], v[0]);
+      v[1] = fmaf(X[lo] * Z[hi], d[lo + 2 + 4 * hi] - d[lo + 4 * hi], v[1]);
+      v[2] = fmaf(X[lo] * Y[hi], d[lo + 2 * hi + 4] - d[lo + 2 * hi], v[2]);
+    }
+    const float kw = key == 0 ? ls.w0 : ls.w1;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) t[a] = fmaf(kw * d3[a], v[a], t[a]);
+  }
+}
+
+// The network and its gradient on the wave's 64 samples: returns the logit of
+// this lane's own sample and leaves its partial gradients (of the logit) in
+// grad[4 lane .. 4 lane + 3].
+template <class CF, int HH>
+__device__ inline float mlp_split_adj(const char* wsm, const char* bsm, const SplitTile& st, f4* grad,
+                                      const LatentSrc& ls) {
+  using SG = SplitGeo<CF>;
+  using SA = SplitAdjGeo<CF>;
+  using P16 = PrecT<kF16>;
+  using PB = PrecT<kBF16>;
+  constexpr int MT = SG::MT, HS = SG::HS, NT = 2;
+  const int lane = threadIdx.x & 63;
+  const int g = lane >> 4, n = lane & 15;
+  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  const float oct = 0.5f * (float)(1 << (SG::OCT * g));
+  const f4* wo = reinterpret_cast<const f4*>(bsm + (HH - 1) * SA::WB + SA::WB0);
+  f4 out[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) out[u] = zero;
+  for (int tp = 0; tp < 4; tp += NT) {
+    SplitPair<CF> sp;
+    sp.layer0(wsm, st, ls, tp);
+    f4 der[HH][NT][MT];
+    const char* p = wsm + SG::L0;
+#pragma unroll
+    for (int i = 0; i < HH; ++i) {
+      if (i > 0) {
+        sp.hidden(p);
+        sp.template pack<true>(reinterpret_cast<const f4*>(p + SG::WH), false, der[i]);
+        p += SG::HID;
+      } else {
+        sp.template pack<true>(reinterpret_cast<const f4*>(wsm + SG::W0F + SG::W0L), true, der[0]);
+      }
+    }
+    sp.output(p, tp, out);
+    // backward: e_i = dy/dh_{i+1} * act'(x_i), dy/dh_i = W_i^T e_i
+    f4 e[NT][MT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) e[u][mt] = wo[4 * mt + g] * der[HH - 1][u][mt];
+    b8 b[3][NT][HS];
+    auto split_e = [&]() {
+#pragma unroll
+      for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int s = 0; s < HS; ++s) {
+          float v[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] = 2 * s + j / 4 < MT ? e[u][2 * s + j / 4 < MT ? 2 * s + j / 4 : 0][j % 4] : 0.0f;
+          split3(v, b[0][u][s], b[1][u][s], b[2][u][s]);
+        }
+    };
+    // rows of one M-tile: the six largest products, smallest first
+    auto mma6 = [&](const char* base, f4 c[NT]) {
+#pragma unroll
+      for (int u = 0; u < NT; ++u) c[u] = zero;
+#pragma unroll
+      for (int s = 0; s < HS; ++s) {
+        const b8* f = reinterpret_cast<const b8*>(base + s * SA::FRAG) + lane;
+        const b8 a0 = f[0], a1 = f[kWave], a2 = f[2 * kWave];
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a2, b[0][u][s], c[u]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a1, b[1][u][s], c[u]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a0, b[2][u][s], c[u]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a1, b[0][u][s], c[u]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a0, b[1][u][s], c[u]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) c[u] = PB::mma(a0, b[0][u][s], c[u]);
+      }
+    };
+#pragma unroll
+    for (int i = HH - 1; i >= 1; --i) {
+      split_e();
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        f4 c[NT];
+        mma6(bsm + (i - 1) * SA::WB + mt * HS * SA::FRAG, c);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) e[u][mt] = c[u] * der[i - 1][u][mt];
+      }
+    }
+    split_e();
+    float v[NT][4 * SA::MB];  // dy/d(input) of this lane's slots
+#pragma unroll
+    for (int m = 0; m < SA::MB; ++m) {
+      f4 c[NT];
+      mma6(bsm + (HH - 1) * SA::WB + m * HS * SA::FRAG, c);
+#pragma unroll
+      for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][4 * m + j] = c[u][j];
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      const int s0 = 16 * (tp + u);
+      const f4 pp = st.pos[s0 + n];
+      float ga[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ga[a] = g == a ? v[u][SG::NF + SG::Q] : 0.0f;
+#pragma unroll
+      for (int k = 0; k < SG::OCT; ++k) {
+        const float wk = k2Pi * (oct * (float)(1 << k));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const float ph = pp[a] * (oct * (float)(1 << k));
+          ga[a] = fmaf(wk, fmaf(v[u][6 * k + a], cos_rev(ph), -v[u][6 * k + 3 + a] * sin_rev(ph)), ga[a]);
+        }
+      }
+      // channels to the lane that holds the quarter's corners, and back
+      float ul[SG::Q], t[3];
+#pragma unroll
+      for (int j = 0; j < SG::Q; ++j)
+        ul[j] = __int_as_float(
+            __builtin_amdgcn_ds_bpermute(4 * (16 * (lane & 3) + (lane >> 2)), __float_as_int(v[u][SG::NF + j])));
+      const int s = s0 + (lane >> 2), gq = lane & 3;
+      if (ls.dtype == kF32) split_latent_vjp<CF, kF32>(st, ls, s, gq, ul, t);
+      else if (ls.dtype == kF16) split_latent_vjp<CF, kF16>(st, ls, s, gq, ul, t);
+      else split_latent_vjp<CF, kU8>(st, ls, s, gq, ul, t);
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        ga[a] += __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (4 * n + g), __float_as_int(t[a])));
+      grad[4 * (s0 + n) + g] = f4{ga[0], ga[1], ga[2], 0.0f};
+    }
+  }
+  const f4* so = reinterpret_cast<const f4*>(wsm + SG::L0 + (HH - 1) * SG::HID + SG::WO);
+  return fmaf(out[0][0] + out[1][0], so[0][0], so[1][0]);
 }
 
 }  // namespace fvsrn_detail

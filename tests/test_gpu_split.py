@@ -125,3 +125,44 @@ def test_split_predicted_gradient(FV):
     gerr = float(np.abs(g.cpu().numpy() - gr).max() / np.abs(gr).max())
     print("split predicted err %.3g grad rel %.3g" % (err, gerr), flush=True)
     assert err <= TOL and gerr <= TOL
+
+
+@pytest.mark.parametrize("c,F,L,H", [(32, 8, 4, 1), (32, 16, 8, 4), (48, 16, 8, 2), (48, 8, 4, 3), (48, 16, 8, 3),
+                                     (48, 8, 4, 4), (32, 16, 8, 5)])
+@pytest.mark.parametrize("grid", ["f32", "f16", "u8"])
+def test_split_adjoint(FV, c, F, L, H, grid):
+    """Adjoint gradients at the layer counts on both sides of the split's limits
+    (registers: H = 4, LDS: c = 48), between keyframes, partial waves, a few
+    points outside the domain; the bound of the FP32 gradients, 1e-5 of the
+    largest."""
+    spec = I.NetSpec(R=6, F=F, L=L, c=c, H=H, K=2)
+    lat, w = I.net_params(spec, 51 + c + H)
+    gnet, onet = _nets(FV, spec, lat, w, grid, [0.0, 2.0])
+    xyz = I.uniform_points(205, 8, -1.05, 1.05)
+    dr, gr = (np.array(v) for v in zip(*(O.density_grad(onet, p, 0.5, mode="rev") for p in xyz.astype(np.float64))))
+    for n in (1, 63, 205):
+        d, g = FV.fvsrn_grad_points(gnet, torch.from_numpy(xyz[:n]).cuda(), 0.5, "f32", mode="adjoint")
+        err = float(np.abs(d.cpu().numpy() - dr[:n]).max())
+        gerr = float(np.abs(g.cpu().numpy() - gr[:n]).max() / max(1.0, np.abs(gr).max()))
+        print("split adjoint c%d F%d H%d %s n%d err %.3g grad rel %.3g" % (c, F, H, grid, n, err, gerr), flush=True)
+        assert err <= TOL and gerr <= TOL
+
+
+@pytest.mark.parametrize("layer,log2", [(0, -30), (1, -30), (2, 3), (3, -40)])
+def test_split_adjoint_weight_ranges(FV, layer, log2):
+    """One layer's weights times 2^log2: deltas far below FP16's range. Relative to
+    the largest gradient; a layer scaled up by 2^k raises the bound by 2^k."""
+    spec = I.NetSpec(R=6, F=8, L=4, c=32, H=3)
+    lat, w = I.net_params(spec, 41)
+    at = 0
+    for i, (o, k) in enumerate(spec.layer_shapes()):
+        if i == layer:
+            w[at:at + o * k] *= np.float32(2.0 ** log2)
+        at += o * k + o
+    gnet, onet = _nets(FV, spec, lat, w)
+    xyz = I.uniform_points(300, 9)
+    _, g = FV.fvsrn_grad_points(gnet, torch.from_numpy(xyz).cuda(), 0.0, "f32", mode="adjoint")
+    gr = np.array([O.density_grad(onet, p, mode="rev")[1] for p in xyz.astype(np.float64)])
+    gerr = float(np.abs(g.cpu().numpy() - gr).max() / np.abs(gr).max())
+    print("split adjoint layer %d x 2^%d grad rel %.3g" % (layer, log2, gerr), flush=True)
+    assert gerr <= TOL * max(1.0, 2.0 ** log2)
