@@ -230,7 +230,9 @@ fvsrn_status fvsrn_eval_points(const fvsrn_net_desc* desc, const fvsrn_params* p
 
 /* Density and its gradient d density / d p at n points (Sec. 6), by
    grad_mode: FVSRN_GRAD_FORWARD differentiates through the network, the
-   Fourier features and the trilinear interpolation in forward mode;
+   Fourier features and the trilinear interpolation in forward mode (an FP32
+   network of up to four layers at many points: in reverse mode where that is
+   built, the same derivative to rounding and faster);
    FVSRN_GRAD_ADJOINT does the same in reverse mode (same availability as in
    fvsrn_render); FVSRN_GRAD_PREDICTED returns outputs 1..3 of a
    num_outputs == 4 network (one plain evaluation). FVSRN_GRAD_CENTRAL is not

@@ -26,6 +26,25 @@ struct AdjEntry {
                     float* out_g, hipStream_t st) {
     return launch_points_t<CF, kShadeAdj, HH>(nd, xyz, n, key, key_w, out_d, out_g, st);
   }
+#if FVSRN_PREC == 0
+  // Points beyond which the adjoint is the faster way to an FP32 forward-mode
+  // gradient; -1: none. The forward-mode kernel takes 16 points per wave and runs in
+  // rounds of as many waves as the GPU holds; the adjoint takes 64, but
+  // stages a second set of weights, so one round is forward mode's. Measured, forward
+  // and adjoint: study network, 28,672 points (one round) 23 / 28 us, 30,000
+  // 39 / 27, 100,003 70 / 28, 10^6 567 / 161; c = 48, F = 16, H = 4: 24,576 37 / 53, 28,672
+  // 63 / 53, 400,000 455 / 320. Above four layers, where the adjoint evaluates layers
+  // twice, it loses at some sizes (c = 48, F = 16, H = 6: 400,000 742 / 1258).
+  static long long forward_limit(const NetDev& nd) {
+    if constexpr (HH <= kSplitAdjLayers) {
+      const int wpb = waves_per_block<CF, kShadeFwd, true>(nd.H);
+      const size_t shm =
+          (size_t)fixed_lds_bytes<CF, kShadeFwd>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, kShadeFwd, true>();
+      if (wpb > 0) return 16ll * wpb * resident_blocks<CF, kShadeFwd, true>(wpb, shm);
+    }
+    return -1;
+  }
+#endif
 };
 
 #define FV_ADJ_H(X, C, F, L, GK)                                                             \
@@ -73,5 +92,17 @@ int FV_PASTE(launch_points_adj_p, FVSRN_PREC)(const NetDev& nd, const float* xyz
 #undef X
   return 1;
 }
+
+#if FVSRN_PREC == 0
+bool forward_by_adjoint_p0(const NetDev& nd, long long n) {
+  if (nd.act != kSine) return false;
+  long long limit = -1;
+#define X(C_, F_, L_, GK_, H_) \
+  if (nd.C == C_ && nd.F == F_ && nd.L == L_ && nd.H == H_) limit = AdjEntry<C_, F_, L_, GK_, H_>::forward_limit(nd);
+  FV_ADJ_ALL(X)
+#undef X
+  return limit >= 0 && n > limit;
+}
+#endif
 
 }  // namespace fvsrn_detail

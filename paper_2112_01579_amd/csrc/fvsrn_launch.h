@@ -156,6 +156,8 @@ int launch_points_p2(const NetDev&, const float*, long long, int, float, float*,
   int launch_render_adj_p##P(const NetDev&, const TFDev&, const ViewBatch&, const MarchDev&, float*,          \
                              unsigned long long*, void*);                                                       \
   int launch_points_adj_p##P(const NetDev&, const float*, long long, int, float, float*, float*, void*);
+// Whether n forward-mode gradients of an FP32 network are left to the adjoint.
+bool forward_by_adjoint_p0(const NetDev&, long long n);
 // Networks with a Fourier matrix (fvsrn_rff.hip) and with a time encoding
 // (fvsrn_time.hip), sine activation: unshaded render and point densities
 // (FP32, FP16, BF16), forward-mode gradients and Phong (FP32, FP16); out_g

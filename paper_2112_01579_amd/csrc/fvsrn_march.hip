@@ -99,6 +99,9 @@ int FV_PASTE(launch_points_p, FVSRN_PREC)(const NetDev& nd, const float* xyz, lo
   if (nd.fmat) return FV_PASTE(launch_points_rff_p, FVSRN_PREC)(nd, xyz, n, key, key_w, out_d, out_g, gmode, stream);
   if (nd.time_enc != 0)
     return FV_PASTE(launch_points_time_p, FVSRN_PREC)(nd, xyz, n, key, key_w, out_d, out_g, gmode, stream);
+#if FVSRN_PREC == 0
+  if (out_g && gmode == 0 && forward_by_adjoint_p0(nd, n)) gmode = 3;
+#endif
   if (out_g && gmode == 3) return FV_PASTE(launch_points_adj_p, FVSRN_PREC)(nd, xyz, n, key, key_w, out_d, out_g, stream);
   // gmode 2: a 4-output network's own gradient, from the value-mode kernel
   const int mode = (out_g != nullptr && gmode == 0) ? kShadeFwd : kShadeNone;

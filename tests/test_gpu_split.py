@@ -166,3 +166,23 @@ def test_split_adjoint_weight_ranges(FV, layer, log2):
     gerr = float(np.abs(g.cpu().numpy() - gr).max() / np.abs(gr).max())
     print("split adjoint layer %d x 2^%d grad rel %.3g" % (layer, log2, gerr), flush=True)
     assert gerr <= TOL * max(1.0, 2.0 ** log2)
+
+
+@pytest.mark.parametrize("c,F,L,H,outputs", [(32, 16, 8, 4, 1), (32, 8, 4, 1, 1), (48, 16, 8, 4, 1), (48, 8, 4, 2, 4),
+                                             (32, 16, 8, 5, 1), (32, 8, 8, 3, 1), (64, 16, 8, 2, 1)])
+@pytest.mark.parametrize("n", [16 * 256, 16 * 256 * 9 + 1, 70001])
+def test_forward_mode_gradients_at_many_points(FV, c, F, L, H, outputs, n):
+    """FP32 forward-mode gradients on both sides of the point count beyond which
+    the adjoint evaluates them, with and without an adjoint kernel for the shape:
+    the FP32 gradients' bound at points spread over the call, the last one
+    among them."""
+    spec = I.NetSpec(R=6, F=F, L=L, c=c, H=H, outputs=outputs)
+    lat, w = I.net_params(spec, 61 + c + H)
+    gnet, onet = _nets(FV, spec, lat, w)
+    xyz = I.uniform_points(n, 10, -1.02, 1.02)
+    d, g = (v.cpu().numpy() for v in FV.fvsrn_grad_points(gnet, torch.from_numpy(xyz).cuda(), 0.0, "f32"))
+    at = np.linspace(0, n - 1, 97).astype(np.int64)
+    dr, gr = (np.array(v) for v in zip(*(O.density_grad(onet, p, 0.0) for p in xyz[at].astype(np.float64))))
+    err, gerr = float(np.abs(d[at] - dr).max()), float(np.abs(g[at] - gr).max() / max(1.0, np.abs(gr).max()))
+    print("forward c%d F%d H%d n%d err %.3g grad rel %.3g" % (c, F, H, n, err, gerr), flush=True)
+    assert err <= TOL and gerr <= TOL and np.isfinite(g).all()
