@@ -169,7 +169,9 @@ typedef struct {
    (Sec. 6), gradients below 1e-6 in length leave rgb unshaded; ka, kd, ks
    and shininess must be finite, non-negative and at most 1e6. For the
    network, grad_mode selects how the gradient is obtained (Sec. 6):
-   FVSRN_GRAD_FORWARD differentiates the network in forward mode;
+   FVSRN_GRAD_FORWARD differentiates the network in forward mode (an FP32
+   network of up to four layers: in reverse mode where that is built, the same
+   derivative to rounding and faster);
    FVSRN_GRAD_CENTRAL takes central differences of the network density with
    step fd_step (> 0, world units): seven network evaluations per sample;
    FVSRN_GRAD_PREDICTED uses outputs 1..3 of a num_outputs == 4 network as the
@@ -200,8 +202,8 @@ typedef struct {
    [0] += samples composited, [1] += rays that hit the domain, [2] += sample
    slots issued (rays per wave x march steps of the wave, idle rays included;
    [0]/[2] is the occupancy of the matrix tiles). A wave's step holds 64
-   samples without shading, 16 with forward-mode gradients and 8 with central
-   differences: one of each of as many rays, or, in launches too small to
+   samples without shading or with the adjoint, 16 with forward-mode gradients
+   (unless evaluated in reverse mode) and 8 with central differences: one of each of as many rays, or, in launches too small to
    fill the GPU so, 2 to 16 consecutive ones of fewer rays. Phong shading needs the density gradient, obtained as
    march->grad_mode selects (Sec. 6), for FP32, FP16 and BF16 networks
    (central differences and predicted gradients for the sine activation,

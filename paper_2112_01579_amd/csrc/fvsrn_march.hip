@@ -74,7 +74,15 @@ int FV_PASTE(launch_render_p, FVSRN_PREC)(const NetDev& nd, const TFDev& tf, con
                                           float* out, unsigned long long* stats, void* stream) {
   if (nd.fmat) return FV_PASTE(launch_render_rff_p, FVSRN_PREC)(nd, tf, vb, m, out, stats, stream);
   if (nd.time_enc != 0) return FV_PASTE(launch_render_time_p, FVSRN_PREC)(nd, tf, vb, m, out, stats, stream);
-  if (m.phong && m.grad_mode == 3) return FV_PASTE(launch_render_adj_p, FVSRN_PREC)(nd, tf, vb, m, out, stats, stream);
+  bool adj = m.phong && m.grad_mode == 3;
+#if FVSRN_PREC == 0
+  // A view's samples are many, and an adjoint step of a wave takes four times
+  // as many as a forward-mode one (ms at forward mode and here, study network:
+  // 200 x 150 4.15 / 1.36, 800 x 600 62.5 / 15.9; c = 48, F = 16, H = 4, whose
+  // adjoint is on the FP32 MFMA: 4.80 / 3.47, 71.7 / 48.8).
+  if (m.phong && m.grad_mode == 0) adj = forward_by_adjoint_p0(nd, 1ll << 40);
+#endif
+  if (adj) return FV_PASTE(launch_render_adj_p, FVSRN_PREC)(nd, tf, vb, m, out, stats, stream);
   const int mode = !m.phong ? kShadeNone : (m.grad_mode == 1 ? kShadeFD : (m.grad_mode == 2 ? kShadePred : kShadeFwd));
   // packed FP16 gathers for an FP16 network on an FP16 or uint8 grid
   const int gk = FVSRN_PREC == 0 ? 0
