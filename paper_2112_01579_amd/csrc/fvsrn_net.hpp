@@ -434,6 +434,93 @@ struct LatentColumnH {
   }
 };
 
+// LatentColumnH for the F = 16 channels of the samples of two adjacent lanes
+// (value lanes, lane n's sample in lane n): first the even lane's sample, then the
+// odd one's, each lane on its half of the channels, so that one L1 lookup
+// serves both halves of a vertex (32 bytes) where a lane's two loads were one
+// each; the sums and their order are the same. Measured, 2^24 random points:
+// study network 449 -> 432 us (492 -> 451 from a cold L2), two keyframes 782 -> 674,
+// c = 48 808 -> 788; the VALU is busy 69% of it then.
+struct LatentPairH {
+  h8 raw[2][8];  // [sample][corner], as loaded
+  float xy[4], z0, z1;
+  unsigned at[2], off[8];
+
+  // the even / odd lane's value in both lanes of the pair
+  template <int ODD>
+  static __device__ inline unsigned of_lane(unsigned x) {
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)x, ODD ? 0xF5 : 0xA0, 0xF, 0xF, true);
+  }
+
+  __device__ inline void begin(const LatentSrc& ls, float px, float py, float pz) {
+    int ix, iy, iz;
+    float fx, fy, fz, dx, dy, dz;
+    axis_cell_h(px, ls.R, ix, fx, dx);
+    axis_cell_h(py, ls.R, iy, fy, dy);
+    axis_cell_h(pz, ls.R, iz, fz, dz);
+    z0 = 1.0f - fz;
+    z1 = fz;
+    const float x0 = 1.0f - fx, y0 = 1.0f - fy;
+    const unsigned R = (unsigned)ls.R;
+    const unsigned base = vertex_offset(ix, iy, iz, 16u, R * 16u, R * R * 16u);
+    corner_offsets(16u, R * 16u, R * R * 16u, off);
+    xy[0] = x0 * y0;
+    xy[1] = fx * y0;
+    xy[2] = x0 * fy;
+    xy[3] = fx * fy;
+    const unsigned half = 16u * (threadIdx.x & 1u);
+    at[0] = of_lane<0>(base) * 2u + half;
+    at[1] = of_lane<1>(base) * 2u + half;
+    load(ls.g0, ls.bytes);
+  }
+
+  __device__ inline void load(const void* g, unsigned bytes) {
+    const __amdgpu_buffer_rsrc_t r = grid_rsrc(g, bytes);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) raw[p][c] = __builtin_bit_cast(h8, load16(r, at[p], off[c] * 2u));
+  }
+
+  template <int P>
+  __device__ inline void sample(const h2 wp[4], h2* z2) const {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const h2 w = __builtin_bit_cast(h2, of_lane<P>(__builtin_bit_cast(unsigned, wp[j])));
+#pragma unroll
+      for (int lo = 0; lo < 2; ++lo) {
+        const h2 w2 = {w[lo], w[lo]};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const h2 v2 = {raw[P][2 * j + lo][2 * k], raw[P][2 * j + lo][2 * k + 1]};
+          z2[4 * P + k] = w2 * v2 + z2[4 * P + k];
+        }
+      }
+    }
+  }
+
+  __device__ inline void accumulate(float kw, h2* z2) const {
+    const float zk[2] = {z0 * kw, z1 * kw};
+    h2 wp[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      wp[j] = __builtin_convertvector((f2{xy[2 * (j & 1)] * zk[j >> 1], xy[2 * (j & 1) + 1] * zk[j >> 1]}), h2);
+    sample<0>(wp, z2);
+    sample<1>(wp, z2);
+  }
+
+  // z2[4 p ..]: this lane's half of the channels of the pair's sample p
+  __device__ inline void finish(const LatentSrc& ls, h2* z2) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) z2[j] = h2{(_Float16)0.0f, (_Float16)0.0f};
+    accumulate(ls.w0, z2);  // w0 = 1 for a single keyframe
+    if (ls.g1) {
+      load(ls.g1, ls.bytes);
+      accumulate(ls.w1, z2);
+    }
+  }
+};
+
 // The same gather in one phase: each corner's loads are consumed as they
 // arrive (the render, whose 8x8 ray tiles mostly hit in L1, keeps 4 waves per
 // SIMD with it).
@@ -609,11 +696,14 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
   for (int j = 0; j < G::KROW; ++j) v[j] = 0.0f;
   constexpr bool packed_latent = CF::G16 && (CF::P == kF16 || (CF::P == kBF16 && CF::GK == 1));
   h2 zh[F / 2];
-  LatentColumnH<F> lch;
+  // the pair's samples share their loads; rows of adjacent lanes are adjacent
+  constexpr bool PAIR = packed_latent && OVERLAP && !GRAD && F == 16;
+  std::conditional_t<PAIR, LatentPairH, LatentColumnH<F>> lch;
   if constexpr (packed_latent && CF::GK == 2) {
     latent_column_q<F>(ls, role, px, py, pz, zh);
   } else if constexpr (packed_latent && OVERLAP) {
-    lch.begin(ls, role, px, py, pz);
+    if constexpr (PAIR) lch.begin(ls, px, py, pz);
+    else lch.begin(ls, role, px, py, pz);
     // keep the Fourier features below between the loads and their use
     __builtin_amdgcn_sched_barrier(0);
   } else if constexpr (packed_latent) {
@@ -743,6 +833,14 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
       if (!done) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = to_e<E>(v[8 * q + j]);
+      }
+      if constexpr (PAIR) {
+        // zh of q = 0, 1 is this lane's half of the pair's sample q
+        const int odd = threadIdx.x & 1;
+        if (q < 2) {
+          reinterpret_cast<V8*>(row + (q - odd) * G::ROW)[odd] = x;
+          continue;
+        }
       }
       dst[q] = x;
     }
