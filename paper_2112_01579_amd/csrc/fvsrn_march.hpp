@@ -511,7 +511,7 @@ __global__ __launch_bounds__((max_waves<CF, PM, true, HH>() * 64)) void points_k
     const bool ok = idx < n;
     const float x = nx, y = ny, z = nz;
     if constexpr (SPLIT) st.put(lane, ls, CF::F, x, y, z);
-    else write_features<CF, GRAD, CF::P != kF32 && CF::GK == 1 && !GRAD>(myrow, ls, role, x, y, z, tfe, nd.fm);
+    else write_features<CF, GRAD, CF::P != kF32 && CF::GK != 2 && !GRAD>(myrow, ls, role, x, y, z, tfe, nd.fm);
     wave_lds_sync();
     load_pos(c + stride);
     if constexpr (ADJ) {

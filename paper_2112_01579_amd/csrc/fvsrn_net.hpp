@@ -356,6 +356,59 @@ __device__ inline void latent_column(const LatentSrc& ls, const LaneRole& role, 
   }
 }
 
+// Value of lane n - n % LANES + K in all of a group of LANES lanes (2 or 4).
+template <int LANES, int K>
+__device__ inline unsigned group_lane(unsigned x) {
+  constexpr int ctrl = LANES == 4 ? K * 0x55 : K * 0x55 + 0xA0;  // K K K K or K K 2+K 2+K
+  return (unsigned)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+}
+
+// latent_column of an FP32 grid for the value lanes of a random point batch:
+// the F / 4 lanes of a group take the group's samples in turn, each lane 4
+// channels, so that one L1 lookup serves a vertex (a lane on its own needs one
+// per 16 bytes: 32 per point, one per CU and cycle, bound 2^24 points at 870 us).
+// z[4 p ..]: this lane's channels of the group's sample p. The sums and their
+// order are latent_column's. Measured, FP16 network, 2^24 points: study 768 -> 576 us,
+// two keyframes 2157 -> 973, c = 48 1362 -> 1306 (bound by its own work).
+template <int F, int P = 0>
+__device__ inline void latent_group(const LatentSrc& ls, unsigned base, const unsigned off[8], const float w[8],
+                                    float* z) {
+  constexpr int LANES = F / 4;
+  const unsigned at = group_lane<LANES, P>(base) * 4u + 16u * (threadIdx.x % LANES);
+#pragma unroll
+  for (int key = 0; key < 2; ++key) {
+    const void* g = key == 0 ? ls.g0 : ls.g1;
+    if (key == 1 && !g) break;
+    const __amdgpu_buffer_rsrc_t r = grid_rsrc(g, ls.bytes);
+    const float kw = key == 0 ? ls.w0 : ls.w1;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float wc = __uint_as_float(group_lane<LANES, P>(__float_as_uint(w[c] * kw)));
+      const float4 v = __builtin_bit_cast(float4, load16(r, at, off[c] * 4u));
+      z[4 * P + 0] = fmaf(wc, v.x, z[4 * P + 0]);
+      z[4 * P + 1] = fmaf(wc, v.y, z[4 * P + 1]);
+      z[4 * P + 2] = fmaf(wc, v.z, z[4 * P + 2]);
+      z[4 * P + 3] = fmaf(wc, v.w, z[4 * P + 3]);
+    }
+  }
+  if constexpr (P + 1 < LANES) latent_group<F, P + 1>(ls, base, off, w, z);
+}
+template <int F>
+__device__ inline void latent_column_group(const LatentSrc& ls, float px, float py, float pz, float* z) {
+  int ix, iy, iz;
+  float fx, fy, fz, dx, dy, dz;
+  axis_cell(px, ls.R, ix, fx, dx);
+  axis_cell(py, ls.R, iy, fy, dy);
+  axis_cell(pz, ls.R, iz, fz, dz);
+  const unsigned R = (unsigned)ls.R;
+  unsigned off[8];
+  corner_offsets((unsigned)F, R * F, R * R * F, off);
+  const float x0 = 1.0f - fx, y0 = 1.0f - fy, z0 = 1.0f - fz;
+  const float w[8] = {x0 * y0 * z0, fx * y0 * z0, x0 * fy * z0, fx * fy * z0,
+                      x0 * y0 * fz, fx * y0 * fz, x0 * fy * fz, fx * fy * fz};
+  latent_group<F>(ls, vertex_offset(ix, iy, iz, (unsigned)F, R * F, R * R * F), off, w, z);
+}
+
 // FP16 variant of latent_column for an FP16 grid feeding an FP16 network:
 // the eight corner products are accumulated pairwise in packed FP16 (each
 // corner is one v_pk_fma per two channels) and land in the input row without
@@ -679,7 +732,8 @@ __device__ inline float time_tau(float t, float lo, float hi, float scale) {
 // Builds this lane's input row at position p and writes it to `row` (LDS).
 // tf: the sample's time inputs (Geo::TIN values; ignored without a time
 // encoding); they do not depend on p, so tangent rows get zeros there.
-// OVERLAP (FP16 network on an FP16 grid): issue the corner loads, build the
+// OVERLAP (random points; FP16 or BF16 network): lanes share vertices (PAIR,
+// GROUP), and on an FP16 grid issue the corner loads, build the
 // Fourier features, then accumulate the corners, so that the features hide
 // the loads' latency; it holds the loaded corners in registers meanwhile
 // (worth it at 3 waves per SIMD, where the random point gathers wait on L2;
@@ -698,6 +752,9 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
   h2 zh[F / 2];
   // the pair's samples share their loads; rows of adjacent lanes are adjacent
   constexpr bool PAIR = packed_latent && OVERLAP && !GRAD && F == 16;
+  // likewise on an FP32 grid (a BF16 network's other grids come here too)
+  constexpr bool GROUP = !packed_latent && OVERLAP && !GRAD && CF::P != kF32;
+  const bool group = GROUP && ls.dtype == kF32;
   std::conditional_t<PAIR, LatentPairH, LatentColumnH<F>> lch;
   if constexpr (packed_latent && CF::GK == 2) {
     latent_column_q<F>(ls, role, px, py, pz, zh);
@@ -708,6 +765,8 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
     __builtin_amdgcn_sched_barrier(0);
   } else if constexpr (packed_latent) {
     latent_column_h<F>(ls, role, px, py, pz, zh);
+  } else if (group) {
+    latent_column_group<F>(ls, px, py, pz, v);
   } else {
     latent_column<F>(ls, role, px, py, pz, v);
   }
@@ -811,6 +870,20 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
   } else {
     using V8 = typename PrecT<CF::P>::VA;
     V8* dst = reinterpret_cast<V8*>(row);
+    if constexpr (GROUP) {
+      if (group) {
+        // v[4 p ..] is this lane's part of the group's sample p
+        using V4 = typename PrecT<CF::P>::VT;
+        const int l = threadIdx.x % (F / 4);
+#pragma unroll
+        for (int p = 0; p < F / 4; ++p) {
+          V4 x;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = to_e<E>(v[4 * p + j]);
+          *reinterpret_cast<V4*>(row + (p - l) * G::ROW + 4 * l) = x;
+        }
+      }
+    }
 #pragma unroll
     for (int q = 0; q < G::KROW / 8; ++q) {
       V8 x;
@@ -833,6 +906,9 @@ __device__ inline void write_features(typename CF::E* row, const LatentSrc& ls, 
       if (!done) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = to_e<E>(v[8 * q + j]);
+      }
+      if constexpr (GROUP) {
+        if (q < F / 8 && group) continue;
       }
       if constexpr (PAIR) {
         // zh of q = 0, 1 is this lane's half of the pair's sample q
