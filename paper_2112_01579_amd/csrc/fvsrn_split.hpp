@@ -27,8 +27,8 @@
 // channels of the tile's sample n, so that only the sample's position, cell
 // and fractions go through LDS (32 bytes a sample instead of a 272-byte row:
 // 12 waves per CU instead of 7). Measured, before and now: 10^6 random points
-// of the study network 145 -> 77 us, 2^24 points 2.14 -> 1.0 ms (17 G/s), its
-// 8 x 1024^2 views 164 -> 80 ms; VALU busy 80% in the render.
+// of the study network 145 -> 71 us, 2^24 points 2.14 -> 0.98 ms (17 G/s), its
+// trained 8 x 1024^2 orbit 331 -> 158 ms; VALU busy 80% in the render.
 #pragma once
 #include "fvsrn_net.hpp"
 

@@ -10,7 +10,7 @@
 //   1. the wave's 64 lanes write the chunk's 16 input rows to LDS, four lanes
 //      per point (write_row_quad);
 //   2. forward through the layers on 16x16x4 FP32 MFMA, keeping every
-//      pre-activation a_i in LDS (sample-major);
+//      pre-activation a_i in LDS (sample-major; delta_i replaces it later);
 //   3. output sigmoid, loss and dL/dy (for a 4-output network fitted with
 //      gradient targets, also the L1 terms of the predicted gradient, Sec. 6);
 //   4. backward: delta_i = (W_{i+1}^T delta_{i+1}) * act'(a_i) on MFMA with
@@ -21,9 +21,11 @@
 // dW tiles are summed per wave over its chunks (no atomics, so dW is bitwise
 // reproducible): the tiles that fit stay in registers, the hidden layers'
 // bias gradients in a small LDS area, the rest are added into the wave's
-// workspace slice; each wave writes its sums to its slice at the end.
+// workspace slice; at the end each wave writes its sums to its slice, or the
+// workgroup's waves add theirs up in LDS and write one slice (FP32, c = 32).
 // slice_sum_kernel and gather_kernel then sum the slices in a fixed order
-// into the packed gradient; adam_kernel applies the update.
+// into the packed gradient; gather_kernel and vertex_sum_kernel apply Adam to
+// what they have just summed (adam_kernel after latent_grad_kernel).
 // The latent gradient is gathered, not scattered: the points are
 // counting-sorted by cell (the cell scan kernels, bin_points_kernel) and every
 // grid vertex sums the trilinear-weighted dL/dz of the points in its (up to)
