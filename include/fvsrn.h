@@ -214,10 +214,10 @@ typedef struct {
    is not available); other combinations return FVSRN_ERR_UNSUPPORTED.
    Predicted gradients need num_outputs == 4.
    Each launch is persistent (as many workgroups as the GPU holds at once)
-   and hands its tiles out through a pair of counters in a static per-GPU
-   array of 1024 pairs; successive calls on a device take successive pairs,
-   so at most 1024 fvsrn_render launches (one per 16 views of a call)
-   may be in flight on one GPU at once. */
+   and, if it has more tiles than waves, hands the rest out through a pair of
+   counters in a static per-GPU array of 1024 pairs; successive such launches on
+   a device take successive pairs, so at most 1024 of them (one per 16
+   views of a call) may be in flight on one GPU at once. */
 fvsrn_status fvsrn_render(const fvsrn_net_desc* desc, const fvsrn_params* params,
                           const fvsrn_tf* tf, const fvsrn_camera* cams, int32_t n_views,
                           const fvsrn_march* march, float* out_rgba,

@@ -130,6 +130,14 @@ constexpr int kLaunchTooLarge = 4;
 int check_launch();                                   // 0 or 2 after a launch
 int grid_blocks(long long work, int per_block, int cap);
 int device_cus();
+// Segments after which early termination can end a ray at the earliest (the
+// transfer function's largest extinction all along it) and does at the latest
+// (its smallest; infinite if it is transparent somewhere, or without early
+// termination). The densities themselves are not known on the host.
+struct RayEnds {
+  double first, last;
+};
+RayEnds ray_ends(const TFDev&, const MarchDev&);
 // Dynamic tile queue of the render launches: a pair of counters [next tile,
 // waves done] on the current device, zero when handed out (the launch that
 // uses it sets it back to zero as its last wave ends). Calls rotate over

@@ -206,9 +206,14 @@ __device__ inline void composite(Accum& acc, const float rgba[4], float len) {
 // with seg_shift > 0 (small launches, see segments_log2), 2^seg_shift
 // consecutive segments of fewer rays, composited by a prefix product over the
 // ray's lanes.
-// Persistent: as many workgroups as the CUs hold at once, each wave taking
-// tiles from a device-wide counter until none is left (queue[0]: the next
-// tile; queue[1]: waves done, so that the last one sets both back to zero).
+// Persistent: as many workgroups as the CUs hold at once, each wave taking the
+// tile of its own index (neighbours, whose rays are alike, on different CUs),
+// then tiles from a device-wide counter until none is left (queue[0]: the next
+// tile; queue[1]: waves done, so that the last one sets both back to zero). A
+// launch with a wave per tile has no queue: the counter is one address for all
+// XCDs and serves a wave in about 12 ns, which bounds launches of rays that end
+// at once (128 x 96 of an opaque volume, 16 segments per step, 3,072 tiles: 117 us
+// with the queue, 18 without; a 64^2 x 128 step view 75 and 47).
 // Tile costs vary (empty, short and long rays): a static share of tiles per
 // wave was measured 30% slower, and one tile per wave keeps a workgroup's
 // LDS until its slowest wave ends, so the CUs ran at two thirds of their
@@ -266,7 +271,9 @@ __global__ __launch_bounds__((max_waves<CF, MODE, false, HH>() * 64)) void march
   double* lray = reinterpret_cast<double*>(wlds + 2 * kWave * sizeof(f4)) + lane;  // SPLIT: this lane's ray
   f4* lgrad = reinterpret_cast<f4*>(wlds + 2 * kWave * sizeof(f4) + kRayBytes);    // and the partial gradients
   unsigned long long n_samp = 0, n_hit = 0, iters = 0;
-  for (int tile = next_tile(queue, lane); tile < n_tiles; tile = next_tile(queue, lane)) {
+  const int n_waves = gridDim.x * wpb;
+  for (int tile = wave * gridDim.x + blockIdx.x; tile < n_tiles;
+       tile = queue ? n_waves + next_tile(queue, lane) : n_tiles) {
     const int v = tile / tiles_per_view;
     const int tr = tile % tiles_per_view;
     const int px = ((tr % tiles_x) << lw) + (rl & ((1 << lw) - 1));
@@ -455,7 +462,7 @@ __global__ __launch_bounds__((max_waves<CF, MODE, false, HH>() * 64)) void march
       atomicAdd(stats + 2, iters * (unsigned long long)(64 / LPR));
     }
   }
-  release_queue(queue, lane, gridDim.x * wpb);
+  if (queue) release_queue(queue, lane, n_waves);
 }
 
 // Point evaluation (PM): kShadeNone -- density, and with out_g set outputs
@@ -570,23 +577,37 @@ __global__ __launch_bounds__((max_waves<CF, PM, true, HH>() * 64)) void points_k
 // (see march_kernel), for `slots` waves resident on the GPU. Tiles of one
 // segment per ray leave a small launch with idle waves and serial rays, and
 // a middle-sized one with few tiles per wave and a long tail, so a ray takes
-// more segments until there are 32 tiles per wave slot: up to 16 while the
-// one-segment tiles are under 4 per slot, else up to 4, since a ray that ends
-// early leaves the rest of its step unused; and never so many that a chord
-// has under 4 steps. Measured, one segment against the rule's, ms per launch:
-// 64^2 x 128 steps FP32 0.561 -> 0.078 (16); FP16 study network 256^2 3.19 ->
-// 0.61 (16), 512^2 3.34 -> 2.01 (16; 8: 1.99), 1024^2 8.50 -> 7.43 (4), 8 x
-// 1024^2 52.2 -> 52.2 (1; 4: 52.3, 16: 54.9); 1920x1080 c = 48 adjoint 48.1 ->
-// 44.9 (4; 8: 44.6).
+// more segments
+//  * while that leaves no more tiles than wave slots (idle waves cost nothing);
+//  * beyond, until there are 32 tiles per wave slot, up to 16 while the
+//    one-segment tiles are under 4 per slot, else up to 4, and no more than the
+//    segments that can end a ray (RayEnds), falling to an eighth of them at
+//    two tiles per slot: a ray that ends early leaves the rest of its step unused,
+//    and every tile costs a ray set-up and a draw. At least 4, or 2 from one to two
+//    tiles per slot, where the transfer function has a transparent part: the
+//    longest rays then set the time;
+//  * never so many that a chord has under 4 steps.
+// Measured, one segment against the rule's, ms per launch (a fitted network's
+// densities, 256 steps per unit): 64^2 x 128 steps FP32 0.561 -> 0.047 (16); FP16 study
+// network 320x240 2.67 -> 0.55, 512x384 2.88 -> 1.19 (16; 8: 1.22), 1024x768 4.5 (16)
+// and 4.3 (8), 8 x 1024^2 52.2 (1; 4: 52.3, 16: 54.9); 1920x1080 c = 48 adjoint 48.1 ->
+// 44.9 (4; 8: 44.6). Rays that end after 3 to 4 samples, before these limits
+// and with them: FP16 320x240 0.318 -> 0.023 (one segment 0.058), 1024x768 2.33 -> 0.21
+// (0.25); after 18 samples 1024x768 2.33 -> 0.38 (0.35).
 template <int MODE>
-int segments_log2(const ViewBatch& vb, const MarchDev& m, long long slots) {
+int segments_log2(const ViewBatch& vb, const MarchDev& m, const RayEnds& ends, long long slots) {
   const int lw = TileShape<MODE>::log_w(0), lh = TileShape<MODE>::log_h(0);
   const long long tiles =
       (long long)((vb.width + (1 << lw) - 1) >> lw) * ((vb.height + (1 << lh) - 1) >> lh) * vb.n_views;
   const double chord = m.fixed_steps > 0 ? m.fixed_steps : 3.4641016 / m.step;  // segments of the longest
   const int most = tiles >= 4 * slots ? 2 : (lw + lh < 4 ? lw + lh : 4);
+  double limit = ends.first / fmin(8.0, fmax(1.0, 4.0 * (double)tiles / (double)slots));
+  if (ends.last < HUGE_VAL) limit = fmin(limit, ends.last / 8);
+  else if (tiles < 2 * slots) limit = fmax(limit, tiles < slots ? 4 : 2);
   int sh = 0;
-  while (sh < most && (tiles << sh) < 32 * slots && (double)(8 << sh) <= chord) ++sh;
+  while (sh < most && (double)(8 << sh) <= chord &&
+         ((tiles << (sh + 1)) <= slots || ((tiles << sh) < 32 * slots && (double)(2 << sh) <= limit)))
+    ++sh;
   return sh;
 }
 
@@ -613,7 +634,7 @@ int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, cons
       (size_t)fixed_lds_bytes<CF, MODE, HH>(nd.H) + (size_t)wpb * wave_lds_bytes<CF, MODE, false, HH>();
   // the workgroups the CUs hold at once, fewer for small launches
   const long long resident = resident_blocks<CF, MODE, false, HH>(wpb, shm);
-  const int sh = segments_log2<MODE>(vb, m, resident * wpb);
+  const int sh = segments_log2<MODE>(vb, m, ray_ends(tf, m), resident * wpb);
   const int tw = 1 << TileShape<MODE>::log_w(sh), th = 1 << TileShape<MODE>::log_h(sh);
   const int tx = (vb.width + tw - 1) / tw, ty = (vb.height + th - 1) / th;
   const long long tiles = (long long)tx * ty * vb.n_views;
@@ -621,8 +642,8 @@ int launch_render_t(const NetDev& nd, const TFDev& tf, const ViewBatch& vb, cons
   const long long want = (tiles + wpb - 1) / wpb;
   const long long blocks = want < resident ? want : resident;
   if (blocks < 1) return 0;
-  unsigned int* queue = tile_queue_slot();
-  if (!queue) return 2;
+  unsigned int* queue = nullptr;
+  if (tiles > blocks * wpb && !(queue = tile_queue_slot())) return 2;
   if (sh > 0 || MODE == kShadeAdj)
     launch_march<CF, MODE, HH, true>(blocks, wpb, shm, nd, tf, vb, m, out, stats, queue, tx, ty, sh, st);
   else

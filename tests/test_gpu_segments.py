@@ -114,3 +114,20 @@ def test_segments_rays_that_miss(FV):
     ref, ns = O.render(O.Field(net=onet), I.ramp_tf(), [cam], m)
     assert float(np.abs(img - ref).max()) <= FP32_TOL and stats[0] == ns
     assert 0 < stats[1] < 41 * 40
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+@pytest.mark.parametrize("mode", [None, 3])
+def test_segments_of_rays_that_end_at_once(FV, prec, mode):
+    """A transfer function of one extinction ends every ray at its fourth sample
+    (exp(-500 / 256 * 4) < 1e-3 < exp(-500 / 256 * 3)), whatever the densities. At over
+    a tile per wave the launch may not spend several times as many slots on it."""
+    gnet, _ = _nets(FV)
+    tf = I.TF(points=((0.0, 0.9, 0.5, 0.1, 1.0), (1.0, 1.0, 0.6, 0.2, 1.0)), opacity_scale=500.0)
+    m = I.March(step=1.0 / 256, ert_eps=1e-3, phong=mode is not None, grad_mode=mode or 0)
+    stats = torch.zeros(3, dtype=torch.int64, device="cuda")
+    img = FV.fvsrn_render(gnet, tf, [I.ortho_camera(640, 640)], m, prec, stats=stats).cpu().numpy()
+    n, rays, slots = stats.cpu().numpy()
+    print("solid %s mode %s: %d samples of %d rays in %d slots" % (prec, mode, n, rays, slots), flush=True)
+    assert rays == 640 * 640 and n == 4 * rays and slots <= 1.5 * n
+    assert float(np.abs(img[..., 3] - (1.0 - np.exp(-500.0 / 256 * 4))).max()) <= 1e-5
