@@ -218,12 +218,13 @@ __global__ __launch_bounds__(kDenseThreads, PHONG ? 4 : 5) void dense_march_kern
     wave_lds_sync();
     for (int k = 0; k < S; ++k) {
       const f4 e = sw[k * R + (lane & (R - 1))];
-      active = active && e[3] >= 0.0f;
+      active = active && !(e[3] < 0.0f);
       const float trn = active ? e[3] : 1.0f;
       const float ta = T * (1.0f - trn);
-      Cr = fmaf(ta, e[0], Cr);
-      Cg = fmaf(ta, e[1], Cg);
-      Cb = fmaf(ta, e[2], Cb);
+      // (not by a weight of 0: behind the ray's end a shade may be infinite)
+      Cr = active ? fmaf(ta, e[0], Cr) : Cr;
+      Cg = active ? fmaf(ta, e[1], Cg) : Cg;
+      Cb = active ? fmaf(ta, e[2], Cb) : Cb;
       A += ta;
       T *= trn;
       n += active ? 1 : 0;
