@@ -428,10 +428,12 @@ __global__ __launch_bounds__((max_waves<CF, MODE, false, HH>() * 64)) void march
         const float before = __shfl_up(inc, LPR, 64), last = __shfl(inc, lane | (((1 << sh) - 1) * LPR), 64);
         const float T = sl ? acc.T * before : acc.T;
         const bool in = comp && !(sl && T < m.ert_eps);
-        const float ta = in ? T * (1.0f - trn) : 0.0f;
+        if (in) {  // not by a weight of 0: behind the ray's end a shade may be infinite
+          const float ta = T * (1.0f - trn);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) acc.C[a] = fmaf(ta, rgba[a], acc.C[a]);
-        acc.A += ta;
+          for (int a = 0; a < 3; ++a) acc.C[a] = fmaf(ta, rgba[a], acc.C[a]);
+          acc.A += ta;
+        }
         acc.T *= last;
         n_samp += in && q == 0 ? 1ull : 0ull;
         i += 1 << sh;

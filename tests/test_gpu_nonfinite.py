@@ -36,3 +36,18 @@ def test_dense_infinity_behind_the_surface(FV, w, h):
             for v in (vol, hidden))
     assert np.isfinite(a).all() and a[..., 3].max() > 0.99
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("w,h", [(32, 24), (90, 60)])
+def test_render_infinity_behind_the_surface(FV, w, h):
+    """The same for the network: latents of 3e38 in every other vertex layer from 0.27
+    units behind the face on give finite densities and infinite gradients."""
+    spec = I.NET_SMALL
+    lat, weights = I.net_params(spec, 51)
+    far = lat.copy().reshape(spec.K, spec.R, spec.R, spec.R, spec.F)
+    far[:, :spec.R - 3:2, ..., 0] = 3e38
+    m = I.March(step=1.0 / 40, ert_eps=1e-3, phong=True, grad_mode=3)
+    a, b = (FV.fvsrn_render(FV.Network(spec, v.reshape(lat.shape), weights), HARD_TF, [I.ortho_camera(w, h)], m,
+                            "f32").cpu().numpy() for v in (lat, far))
+    assert np.isfinite(a).all() and a[..., 3].max() > 0.99
+    assert np.array_equal(a, b)
