@@ -4,7 +4,7 @@
 // bound by the matrix cores (study network: 360 16x16x4 MFMAs = 11,520 cycles
 // per 64 samples). Every operand here is instead the sum of two FP16 values,
 // x = hi + lo with hi = fp16(x), lo = fp16(x - hi), and each product is
-// hi hi + hi lo + lo hi, accumulated in FP32 (lo lo, below 2^-24 of the
+// hi hi + hi lo + lo hi, accumulated in FP32 (lo lo, at most 2^-22 of the
 // product, is left out): 132 FP16 MFMAs and 40 FP32 ones = 3,400 cycles.
 // Two FP16 mantissas and the sign of lo hold 23 of FP32's 24 bits, provided
 // that lo stays clear of FP16's smallest step of 2^-24:
@@ -13,8 +13,11 @@
 //    sine instruction's own error;
 //  * A operands are weights, scaled per output row by the power of two that
 //    puts the row's largest into [2^13, 2^14); the accumulator is multiplied
-//    by the inverse (exact) in the FMA that adds the bias. (A row that holds
-//    an infinity or NaN is not scaled and gives NaN.)
+//    by the inverse (exact) in the FMA that adds the bias. A hidden row that
+//    holds an infinity or NaN is not scaled and gives NaN, as the sine of the
+//    infinite sum does in FP32. An output row with infinities becomes their
+//    signs times an infinite scale: the logit is infinite and the density 0 or 1, as
+//    in FP32 (several infinities: by the sign of their channels' sum).
 //  * inputs without a bound -- the latent vector and the position -- and their
 //    weights stay on the FP32 MFMA, where they are off the VALU's path.
 // Measured against FP64 (see the tests) the densities are no further off than
@@ -109,7 +112,7 @@ __device__ void stage_split(const NetDev& nd, char* smem) {
     }
     if (l == 0) {
       float* dst = reinterpret_cast<float*>(i == 0 ? smem + SG::W0F + SG::W0L : (i < H ? hid(i) + SG::WH : out + SG::WO));
-      dst[o] = row_unscale(m);
+      dst[o] = i == H && !(m < HUGE_VALF) ? m : row_unscale(m);
     }
   }
   __syncthreads();
@@ -180,7 +183,14 @@ __device__ void stage_split(const NetDev& nd, char* smem) {
     const int lane = e & 63, s = (e >> 6) % HS, t = (e >> 6) / HS;
     const int o = (lane & 15) - 4 * t;  // output o of N-tile t sits in row 4t + o
     float v[8] = {};
-    if (o >= 0 && o < NO) load8k(Wo + o * C, s, lane >> 4, pow2_inverse(so[o]), v);
+    if (o >= 0 && o < NO) {
+      // a row with infinities: they become +-1, the others (all but) 0
+      const bool inf = so[o] == HUGE_VALF;
+      const float most = inf ? 1.0f : 65504.0f;
+      load8k(Wo + o * C, s, lane >> 4, inf ? 0x1p-126f : pow2_inverse(so[o]), v);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __builtin_amdgcn_fmed3f(v[j], -most, most);
+    }
     put(out, e >> 6, lane, v);
   }
   if (tid < 4) so[4 + tid] = tid < NO ? Wo[NO * C + tid] : 0.0f;

@@ -51,3 +51,57 @@ def test_render_infinity_behind_the_surface(FV, w, h):
                             "f32").cpu().numpy() for v in (lat, far))
     assert np.isfinite(a).all() and a[..., 3].max() > 0.99
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("c,F,L,H,outputs", [(32, 8, 4, 3, 1), (32, 16, 8, 1, 1), (48, 16, 8, 2, 4), (64, 8, 4, 5, 1)])
+def test_infinite_output_weight(FV, c, F, L, H, outputs, sign):
+    """One infinite weight of the density's output row: the logit is an infinity
+    of the sign of its channel's activation, the density 0 or 1."""
+    spec = I.NetSpec(R=5, F=F, L=L, c=c, H=H, outputs=outputs)
+    lat, w = I.net_params(spec, 81 + c)
+    big = w.copy()
+    at = w.size - (c + 1) * outputs + 7  # output 0's weight of channel 7
+    big[at] = sign * 1e6  # finite, in the oracle: saturates the sigmoid all the same
+    onet = O.Net(spec, lat, big)
+    xyz = I.uniform_points(500, 82)
+    want = O.eval_points(onet, xyz)
+    sure = (want < 1e-6) | (want > 1.0 - 1e-6)
+    big = w.copy()
+    big[at] = sign * np.inf
+    d = FV.fvsrn_eval_points(FV.Network(spec, lat, big), torch.from_numpy(xyz).cuda()).cpu().numpy()
+    assert sure.sum() > 450 and np.array_equal(d[sure], np.round(want[sure]).astype(np.float32))
+    if H <= 2:  # the same density from the adjoint
+        d2, _ = FV.fvsrn_grad_points(FV.Network(spec, lat, big), torch.from_numpy(xyz).cuda(), mode="adjoint")
+        assert np.array_equal(d2.cpu().numpy()[sure], np.round(want[sure]).astype(np.float32))
+
+
+def test_infinite_output_weights(FV):
+    """Two infinite weights of one sign, channels of one sign: that infinity."""
+    spec = I.NetSpec(R=5, F=8, L=4, c=32, H=2)
+    lat, w = I.net_params(spec, 87)
+    xyz = I.uniform_points(400, 88)
+    h = []  # channels 3 and 20 of the last layer, from networks that return them
+    for ch in (3, 20):
+        one = w.copy()
+        one[-33:-1] = 0.0
+        one[-33 + ch] = 1.0
+        h.append(O.eval_points(O.Net(spec, lat, one), xyz) - 0.5)
+    same = (np.abs(h[0]) > 1e-5) & (np.abs(h[1]) > 1e-5) & (np.sign(h[0]) == np.sign(h[1]))
+    big = w.copy()
+    big[-33 + 3] = big[-33 + 20] = np.inf
+    d = FV.fvsrn_eval_points(FV.Network(spec, lat, big), torch.from_numpy(xyz).cuda()).cpu().numpy()
+    assert same.sum() > 100 and np.array_equal(d[same], (h[0][same] > 0).astype(np.float32))
+
+
+def test_nan_weight(FV):
+    """A NaN in any layer reaches every density."""
+    spec = I.NetSpec(R=5, F=8, L=4, c=32, H=3)
+    lat, w = I.net_params(spec, 83)
+    xyz = torch.from_numpy(I.uniform_points(100, 84)).cuda()
+    at = 0
+    for o, i in spec.layer_shapes():
+        bad = w.copy()
+        bad[at + o * i - 1] = np.nan
+        assert torch.isnan(FV.fvsrn_eval_points(FV.Network(spec, lat, bad), xyz)).all()
+        at += o * i + o
