@@ -1624,7 +1624,7 @@ __global__ void cell_partials_kernel(const float* xyz, int R, long long ncell, i
 #pragma unroll
     for (int b = 0; b < 8; ++b) acc[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     // four points at a time, so that their loads are in flight together; past
-    // the last one a point is read again with weight zero
+    // the last one a point is read again and its gradient taken as zero
     const int end = off[c + 1];
     for (int s = off[c] + sub; s < end; s += 4 * nsub) {
       int p[4];
@@ -1637,6 +1637,7 @@ __global__ void cell_partials_kernel(const float* xyz, int R, long long ncell, i
 #pragma unroll
         for (int a = 0; a < 3; ++a) x[k][a] = xyz[3 * (long long)p[k] + a];
         d[k] = reinterpret_cast<const f4*>(dz + (long long)p[k] * F)[qd];
+        if (s + k * nsub >= end) d[k] = f4{0.0f, 0.0f, 0.0f, 0.0f};
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -1645,11 +1646,10 @@ __global__ void cell_partials_kernel(const float* xyz, int R, long long ncell, i
         axis_cell(x[k][0], R, ix, fx);
         axis_cell(x[k][1], R, iy, fy);
         axis_cell(x[k][2], R, iz, fz);
-        const float on = s + k * nsub < end ? 1.0f : 0.0f;
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
           const int bx = b & 1, by = (b >> 1) & 1, bz = b >> 2;
-          const float w = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz) * on;
+          const float w = (bx ? fx : 1.0f - fx) * (by ? fy : 1.0f - fy) * (bz ? fz : 1.0f - fz);
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[b][j] = fmaf(w, d[k][j], acc[b][j]);
         }

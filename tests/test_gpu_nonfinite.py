@@ -105,3 +105,23 @@ def test_nan_weight(FV):
         bad[at + o * i - 1] = np.nan
         assert torch.isnan(FV.fvsrn_eval_points(FV.Network(spec, lat, bad), xyz)).all()
         at += o * i + o
+
+
+@pytest.mark.parametrize("n", [1, 3, 6])
+def test_overflowing_latent_gradient(FV, n):
+    """n copies of a point whose dL/dz overflows: its cell's vertices take infinite
+    sums, no NaN, however many points a lane sums at a time. (One hidden unit has
+    weight, so that no infinities of two signs meet.)"""
+    spec = I.NetSpec(R=3, F=8, L=4, c=32, H=1)
+    lat, w = I.net_params(spec, 85)
+    W0 = w[:32 * spec.K0].reshape(32, spec.K0)
+    W0[:, 3:3 + 8] = 1e4
+    w[-33:-1] = 0.0
+    w[-33] = 1.0
+    net = FV.Network(spec, lat, w)
+    xyz = np.tile(np.float32([0.13, 0.37, 0.22]), (n, 1))
+    up = np.full(n, 3e38, np.float32)
+    d_lat, d_w = torch.empty_like(net.latent), torch.empty_like(net.weights)
+    FV.fvsrn_train_step(net, d_lat, d_w, torch.from_numpy(xyz).cuda(), dloss_dy=torch.from_numpy(up).cuda())
+    g = d_lat.cpu().numpy().reshape(3, 3, 3, 8)
+    assert not np.isnan(g).any() and np.isinf(g[1:, 1:, 1:]).all()
