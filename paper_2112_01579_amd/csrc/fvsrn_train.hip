@@ -1238,9 +1238,11 @@ __device__ inline void adam_update(const AdamDev& a, long long i, float gi) {
   a.p[i] -= a.lr_bc1 * mi / (sqrtf(vi) * a.inv_sqrt_bc2 + a.eps);
 }
 
-// The same on four neighbouring entries.
+// The same on four neighbouring entries. The moments come from the caller's
+// optimiser state and need only a float's alignment.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline void adam_update4(const AdamDev& a, long long i, f4 g) {
-  f4 m = *reinterpret_cast<const f4*>(a.m + i), v = *reinterpret_cast<const f4*>(a.v + i),
+  f4 m = *reinterpret_cast<const f4u*>(a.m + i), v = *reinterpret_cast<const f4u*>(a.v + i),
      p = *reinterpret_cast<const f4*>(a.p + i);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -1248,8 +1250,8 @@ __device__ inline void adam_update4(const AdamDev& a, long long i, f4 g) {
     v[j] = a.b2 * v[j] + (1.0f - a.b2) * g[j] * g[j];
     p[j] -= a.lr_bc1 * m[j] / (sqrtf(v[j]) * a.inv_sqrt_bc2 + a.eps);
   }
-  *reinterpret_cast<f4*>(a.m + i) = m;
-  *reinterpret_cast<f4*>(a.v + i) = v;
+  *reinterpret_cast<f4u*>(a.m + i) = m;
+  *reinterpret_cast<f4u*>(a.v + i) = v;
   *reinterpret_cast<f4*>(a.p + i) = p;
 }
 

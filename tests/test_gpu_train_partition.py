@@ -115,3 +115,40 @@ def test_train_adam_in_gradient_kernels(FV, K, R):
         assert np.abs(p.cpu().numpy() - p64).max() <= 1e-6
         assert np.abs(opt[m].cpu().numpy() - m64).max() <= 1e-6 * np.abs(m64).max()
         assert np.abs(opt[v].cpu().numpy() - v64).max() <= 1e-6 * np.abs(v64).max()
+
+
+def _adam_step(FV, spec, kt, offset):
+    """One step with moments in one flat buffer, `offset` floats into it."""
+    lat, w = I.net_params(spec, 75)
+    gnet = FV.Network(spec, lat, w, kt)
+    rng = np.random.default_rng(76)
+    n = 900
+    xyz, target = I.uniform_points(n, 77), rng.uniform(0.0, 1.0, n).astype(np.float32)
+    size = 2 * (spec.n_latent + spec.n_weights) + 4
+    flat = torch.zeros(size, device="cuda")
+    at, opt = offset, dict(lr_grid=1e-2, lr_mlp=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, step=3)
+    for k in ("m_latent", "v_latent", "m_weights", "v_weights"):
+        m = spec.n_latent if "latent" in k else spec.n_weights
+        opt[k] = flat[at:at + m]
+        opt[k].copy_(torch.from_numpy(rng.uniform(1e-9, 1e-8, m).astype(np.float32)))
+        at += m
+    d_lat, d_w = torch.empty_like(gnet.latent), torch.empty_like(gnet.weights)
+    times = None if kt is None else torch.from_numpy(rng.uniform(0.0, 2.0, n).astype(np.float32)).cuda()
+    FV.fvsrn_train_step(gnet, d_lat, d_w, torch.from_numpy(xyz).cuda(), target=torch.from_numpy(target).cuda(), adam=opt,
+                        times=times)
+    return [t.cpu().numpy() for t in (gnet.latent, gnet.weights, opt["m_latent"], opt["v_latent"], opt["m_weights"],
+                                      opt["v_weights"], flat[:offset], flat[at:])]
+
+
+@pytest.mark.parametrize("K", [1, 3])
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_train_moments_at_any_float(FV, K, offset):
+    """Moments that are views into a flat optimiser buffer, at no 16-byte boundary: the
+    update of aligned ones (d_latent's sums may differ in their order, so to
+    rounding), and nothing written beside them."""
+    spec = I.NetSpec(R=7, F=8, L=4, c=32, H=2, K=K)
+    kt = [0.0, 1.0, 2.0] if K > 1 else None
+    a, b = _adam_step(FV, spec, kt, 0), _adam_step(FV, spec, kt, offset)
+    for x, y in zip(a[:6], b[:6]):
+        assert np.abs(x - y).max() <= 1e-6 * np.abs(x).max()
+    assert (b[6] == 0.0).all() and (b[7] == 0.0).all()
