@@ -1705,11 +1705,14 @@ struct TrainEntry {
   // Waves of a launch whose workgroups hold at most `fit`, and the waves per
   // workgroup. FP32: no more waves than are resident at once (a workgroup takes
   // a whole CU's LDS, so a launch of more workgroups than CUs runs a second
-  // round for the few that are left); FP16 keeps the partition's bound. Spread
+  // round for the few that are left), and not five to a CU, where the SIMD with two
+  // sets the time (32^3 x 16, H = 6, 2^20 points: 1072 us with five, 991 with four);
+  // FP16 keeps the partition's bound. Spread
   // over all CUs, but at least four to a workgroup, which stage its weights
   // together.
   static void partition(long long n, int fit, bool half, int* nw, int* wpb) {
     const int cus = device_cus(), most = max_waves(n);
+    if (!half && fit == 5) fit = 4;
     *nw = half || most < cus * fit ? most : cus * fit;
     const int spread = (*nw + cus - 1) / cus, least = fit < 4 ? fit : 4;
     *wpb = spread < least ? least : (spread < fit ? spread : fit);
@@ -1812,24 +1815,26 @@ struct TrainEntry {
       if ((rc = check_launch())) return rc;
     }
     const int sl = TC::slice(H), per = TC::kBlockSum && !half ? wpb : 1, count_sl = (nw + per - 1) / per;
-    // the group partials go behind the launch's slices: groups of 32 slices (of
-    // 256 for a slice per wave: the order of the FP16 step's sums), larger ones
-    // where that space is short
-    const int space = slices(n) - nw, least = (count_sl + space - 1) / space, want = per > 1 ? 32 : 256;
+    // the group partials go to the end of the slices' space, behind the launch's
+    // slices: groups of 32 slices (of 256 for a slice per wave: the order of the
+    // FP16 step's sums), larger ones where that space is short
+    const int space = slices(n) - max_waves(n), least = (count_sl + space - 1) / space, want = per > 1 ? 32 : 256;
     const int group = least > want ? least : want;
     const int ng = (count_sl + group - 1) / group;
-    float* partial = (float*)ws + (size_t)nw * sl;
+    float* partial = (float*)ws + (size_t)(slices(n) - ng) * sl;
     hipLaunchKernelGGL(slice_sum_kernel, dim3((sl + 255) / 256, ng), dim3(256), 0, st, (const float*)ws, count_sl,
                        (size_t)per * sl, sl, group, partial);
     rc = check_launch();
     if (rc) return rc;
     // the latent gradient; the two-pass form writes its cell-corner sums over
-    // the wave slices, which slice_sum_kernel has finished reading
+    // the wave slices, which slice_sum_kernel has finished reading, where they
+    // fit the partition's bound (deep networks launch fewer waves, but the space is
+    // there: 32^3 x 16, c = 32, H = 6, 2^20 points 1147 us in one pass, 1072 in two)
     const long long nv = (long long)nd.R * nd.R * nd.R;
     // point subsets per cell: about one per 16 points of an average cell, at most 8
     int sub_log2 = 0;
     while (sub_log2 < 3 && (16LL << sub_log2) * ncell < n) ++sub_log2;
-    if (nd.K == 1 && ((long long)ncell * 8 * F << sub_log2) <= (long long)nw * sl) {
+    if (nd.K == 1 && ((long long)ncell * 8 * F << sub_log2) <= (long long)max_waves(n) * sl) {
       hipLaunchKernelGGL((cell_partials_kernel<F>),
                          dim3(grid_blocks(((long long)ncell << sub_log2) * (F / 4), 256, device_cus() * 32)), dim3(256),
                          0, st, xyz, nd.R, (long long)ncell, sub_log2, (const int*)off, (const int*)order,

@@ -152,3 +152,21 @@ def test_train_moments_at_any_float(FV, K, offset):
     for x, y in zip(a[:6], b[:6]):
         assert np.abs(x - y).max() <= 1e-6 * np.abs(x).max()
     assert (b[6] == 0.0).all() and (b[7] == 0.0).all()
+
+
+@pytest.mark.parametrize("F,L,H,R,n", [(16, 8, 4, 32, 1 << 18), (16, 8, 6, 32, 1 << 20), (8, 4, 8, 64, 1 << 18)])
+def test_train_two_pass_latent_gradient(FV, F, L, H, R, n):
+    """Sparse single-keyframe grids sum per cell and corner first wherever the
+    workspace holds those sums, in deep networks too, whose launches have fewer
+    waves than the workspace has slices."""
+    spec = I.NetSpec(R=R, F=F, L=L, c=32, H=H)
+    lat, w = I.net_params(spec, 78)
+    gnet = FV.Network(spec, lat, w)
+    xyz, target = torch.rand(n, 3, device="cuda") * 2 - 1, torch.rand(n, device="cuda")
+    d_lat, d_w = torch.empty_like(gnet.latent), torch.empty_like(gnet.weights)
+    ws = torch.empty(FV.fvsrn_train_workspace_size(spec, n), dtype=torch.uint8, device="cuda")
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        FV.fvsrn_train_step(gnet, d_lat, d_w, xyz, target=target, workspace=ws)
+        torch.cuda.synchronize()
+    names = " ".join(e.key for e in prof.key_averages())
+    assert "cell_partials_kernel" in names and "latent_grad_kernel" not in names
