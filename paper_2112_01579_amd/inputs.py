@@ -30,7 +30,6 @@ Workloads (stand-ins for the paper's datasets, which are not available):
 from __future__ import annotations
 
 import dataclasses
-import functools
 import math
 from typing import List, Optional, Sequence, Tuple
 
@@ -74,9 +73,10 @@ class NetSpec:
         shapes = [(self.c, self.K0)] + [(self.c, self.c)] * (self.H - 1) + [(self.outputs, self.c)]
         return shapes
 
-    @functools.cached_property
+    @property
     def n_weights(self) -> int:
-        return sum(o * i + o for o, i in self.layer_shapes())
+        c = self.c
+        return c * (self.K0 + 1) + ((self.H - 1) * c + self.outputs) * (c + 1)
 
     @property
     def n_latent(self) -> int:

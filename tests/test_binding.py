@@ -96,3 +96,11 @@ def test_autograd_function_refuses_foreign_parameters(no_lib):
     net = cpu_net()
     with pytest.raises(FV.FvsrnArgumentError, match="own tensors"):
         FvsrnPoints.apply(torch.zeros((4, 3)), net.latent.clone(), net.weights, net, 0.0, "f32")
+
+
+def test_net_spec_keeps_nothing_but_its_fields():
+    """A specification's fields make another one, also after its counts were read."""
+    for c, H, outputs, time_enc in ((32, 1, 1, 0), (48, 4, 4, 0), (64, 8, 1, 3)):
+        spec = I.NetSpec(R=5, F=8, L=4, c=c, H=H, outputs=outputs, time_enc=time_enc)
+        assert spec.n_weights == sum(o * i + o for o, i in spec.layer_shapes())
+        assert I.NetSpec(**vars(spec)) == spec
