@@ -112,3 +112,34 @@ def test_ssim_tile_edges(FV, w, h):
     for i in range(2):
         _, ref = O.ssim(a[i], b[i], with_map=True)
         assert got[i].shape == ref.shape and float(np.abs(got[i] - ref).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("axis", ["x", "z", "xz"])
+@pytest.mark.parametrize("per_unit", [3, 6, 12, 24, 40])
+def test_dense_segments_by_chord(FV, axis, per_unit):
+    """A small launch takes 4, 8, 16, 32 and 64 segments per step, from a longest
+    chord of 16, 32, 64 and 128 segments on (10, 21, 42, 83 and 139 here)."""
+    vol, cam, m = _vol(), _cam(axis, 39, 23), I.March(step=1.0 / per_unit)
+    img, stats = _render(FV, vol, [cam], m)
+    ref, ns = O.render(O.Field(vol=vol), I.ramp_tf(), [cam], m)
+    assert float(np.abs(img - ref).max()) <= TOL and stats[0] == ns and stats[2] == ns
+
+
+@pytest.mark.parametrize("phong", [False, True])
+@pytest.mark.parametrize("axis", ["x", "z"])
+def test_dense_rays_that_end_at_once(FV, axis, phong):
+    """Every ray ends at its fourth sample, in a launch too large for idle waves: two
+    segments per step. A transparent part below all densities takes the launch to
+    more of them: the same image and counts, bit for bit."""
+    ends = ((0.0, 0.9, 0.5, 0.1, 1.0), (1.0, 0.1, 0.6, 0.9, 1.0))
+    vol, cam = _vol(), _cam(axis, 256, 192)
+    m = I.March(step=1.0 / 256, ert_eps=1e-3, phong=phong)
+    out = []
+    for tf in (I.TF(points=ends, opacity_scale=500.0),
+               I.TF(points=((-2.0, 0.9, 0.5, 0.1, 0.0), (-1.0, 0.9, 0.5, 0.1, 1.0)) + ends, opacity_scale=500.0)):
+        stats = torch.zeros(3, dtype=torch.int64, device="cuda")
+        img = FV.fvsrn_render_dense(torch.from_numpy(vol).cuda(), tf, [cam], m, stats=stats).cpu().numpy()
+        out.append((img, stats.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    n, rays, _ = out[0][1]
+    assert rays > 5000 and 3.9 * rays <= n <= 4 * rays  # a grazing ray's chord may be shorter

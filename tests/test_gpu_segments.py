@@ -131,3 +131,48 @@ def test_segments_of_rays_that_end_at_once(FV, prec, mode):
     print("solid %s mode %s: %d samples of %d rays in %d slots" % (prec, mode, n, rays, slots), flush=True)
     assert rays == 640 * 640 and n == 4 * rays and slots <= 1.5 * n
     assert float(np.abs(img[..., 3] - (1.0 - np.exp(-500.0 / 256 * 4))).max()) <= 1e-5
+
+
+# Networks whose forward-mode Phong has a kernel of its own (four lanes per sample): the
+# FP16 passes, FP32 above four layers, and a shape without an adjoint.
+FORWARD = [("f16", I.NET_SMALL, 1e-2), ("f32", dataclasses.replace(I.NET_SMALL, H=5), PHONG32_TOL),
+           ("f32", I.NetSpec(R=9, F=16, L=4, c=32, H=2), PHONG32_TOL)]
+
+
+def _forward_net(FV, spec):
+    lat, w = I.net_params(spec, 52)
+    return FV.Network(spec, lat, w), O.Net(spec, lat, w)
+
+
+@pytest.mark.parametrize("prec,spec,tol", FORWARD)
+def test_segments_forward_mode(FV, prec, spec, tol):
+    """1, 2, 4, 8 and 16 segments of a ray per step, 16 samples per wave step: the
+    slots issued are multiples of 16, and not of the other kernels' 64."""
+    gnet, onet = _forward_net(FV, spec)
+    odd = 0
+    for per_unit in PER_UNIT:
+        m = I.March(step=1.0 / per_unit, phong=True)
+        img, stats = _render(FV, gnet, _cams(), m, prec)
+        ref, _ = O.render(O.Field(net=onet), I.ramp_tf(), _cams(), m)
+        _, ns = O.render(O.Field(net=onet), I.ramp_tf(), _cams(), I.March(step=1.0 / per_unit))
+        err = float(np.abs(img - ref).max())
+        print("segments forward %s H%d 1/%d err %.3g" % (prec, spec.H, per_unit, err), flush=True)
+        assert err <= tol and stats[0] == ns and stats[2] % 16 == 0
+        odd += stats[2] % 64 != 0
+    assert odd > 0
+
+
+@pytest.mark.parametrize("prec,spec,tol", FORWARD)
+@pytest.mark.parametrize("per_unit", [3, 6, 40])
+def test_segments_forward_mode_termination(FV, prec, spec, tol, per_unit):
+    gnet, onet = _forward_net(FV, spec)
+    cams, eps = _cams(), 0.3
+    img, stats = _render(FV, gnet, cams, I.March(step=1.0 / per_unit, ert_eps=eps, phong=True), prec)
+    near = 1e-4 if prec == "f32" else 1e-2  # of T around eps, by the densities' error
+    refs = [O.render(O.Field(net=onet), I.ramp_tf(), cams, I.March(step=1.0 / per_unit, ert_eps=e, phong=True))
+            for e in (eps, eps * (1 - near), eps * (1 + near))]
+    err = np.min([np.abs(img - r).max(-1) for r, _ in refs], axis=0)
+    counts = [O.render(O.Field(net=onet), I.ramp_tf(), cams, I.March(step=1.0 / per_unit, ert_eps=e))[1]
+              for e in (eps * (1 + near), eps * (1 - near))]
+    print("segments forward ERT %s H%d 1/%d err %.3g" % (prec, spec.H, per_unit, err.max()), flush=True)
+    assert float(err.max()) <= tol and min(counts) <= stats[0] <= max(counts)

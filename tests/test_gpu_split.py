@@ -186,3 +186,16 @@ def test_forward_mode_gradients_at_many_points(FV, c, F, L, H, outputs, n):
     err, gerr = float(np.abs(d[at] - dr).max()), float(np.abs(g[at] - gr).max() / max(1.0, np.abs(gr).max()))
     print("forward c%d F%d H%d n%d err %.3g grad rel %.3g" % (c, F, H, n, err, gerr), flush=True)
     assert err <= TOL and gerr <= TOL and np.isfinite(g).all()
+
+
+def test_split_largest_network(FV):
+    """c = 64, F = 16, L = 8, H = 8: one wave per CU beside its 153 KB of fragments, for
+    points and for a view."""
+    spec = I.NetSpec(R=5, F=16, L=8, c=64, H=8)
+    lat, w = I.net_params(spec, 93)
+    gnet, onet = _nets(FV, spec, lat, w)
+    assert _density_error(FV, spec, lat, w, 20001) <= TOL
+    cams, m = I.orbit_cameras(2, 9, 7), I.March(step=1.0 / 20)
+    img = FV.fvsrn_render(gnet, I.ramp_tf(), cams, m).cpu().numpy()
+    ref, _ = O.render(O.Field(net=onet), I.ramp_tf(), cams, m)
+    assert float(np.abs(img - ref).max()) <= TOL
