@@ -52,8 +52,17 @@ def _round_fields(obj, names):
         v = getattr(obj, n)
         object.__setattr__(obj, n, tuple(_f32(x) for x in v) if isinstance(v, tuple) else _f32(v))
 
+class _Counted:
+    # a count that every call reads, kept beside the fields: not in __dict__, which
+    # holds what makes another instance, nor in pickles and copies
+    __slots__ = ("_n_weights",)
+
+    def __getstate__(self):
+        return self.__dict__
+
+
 @dataclasses.dataclass(frozen=True)
-class NetSpec:
+class NetSpec(_Counted):
     R: int            # latent vertices per axis
     F: int            # latent channels
     L: int            # Fourier octaves
@@ -75,8 +84,11 @@ class NetSpec:
 
     @property
     def n_weights(self) -> int:
-        c = self.c
-        return c * (self.K0 + 1) + ((self.H - 1) * c + self.outputs) * (c + 1)
+        try:
+            return self._n_weights
+        except AttributeError:
+            object.__setattr__(self, "_n_weights", sum(o * i + o for o, i in self.layer_shapes()))
+            return self._n_weights
 
     @property
     def n_latent(self) -> int:

@@ -2,6 +2,10 @@
 shape, layout or device) before any library call, so a host pointer or a
 float64 buffer never reaches a kernel. Runs without a GPU: the library is
 replaced by a stub that fails the test if it is called."""
+import copy
+import dataclasses
+import pickle
+
 import numpy as np
 import pytest
 import torch
@@ -99,8 +103,10 @@ def test_autograd_function_refuses_foreign_parameters(no_lib):
 
 
 def test_net_spec_keeps_nothing_but_its_fields():
-    """A specification's fields make another one, also after its counts were read."""
+    """A specification's fields make another one, also after its count was read, as do
+    copies and pickles of it."""
     for c, H, outputs, time_enc in ((32, 1, 1, 0), (48, 4, 4, 0), (64, 8, 1, 3)):
         spec = I.NetSpec(R=5, F=8, L=4, c=c, H=H, outputs=outputs, time_enc=time_enc)
         assert spec.n_weights == sum(o * i + o for o, i in spec.layer_shapes())
-        assert I.NetSpec(**vars(spec)) == spec
+        assert I.NetSpec(**vars(spec)) == spec == copy.copy(spec) == pickle.loads(pickle.dumps(spec))
+        assert dataclasses.replace(spec, H=2).n_weights == I.NetSpec(**{**vars(spec), "H": 2}).n_weights
