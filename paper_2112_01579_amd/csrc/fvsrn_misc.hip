@@ -4,6 +4,7 @@
 #include <stdio.h>
 
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
 #include "fvsrn_common.hpp"
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(kDenseThreads, PHONG ? 4 : 5) void dense_march_kern
     for (int q = 0; q < Q; ++q) {
       const int r = q * G + rl;
       if constexpr (PHONG) {
-        if (has[q]) {
+        if (m.phong && has[q]) {
           const float sx = px3[q][0], sy = px3[q][1], sz = px3[q][2];
           const float gx = (sample(sx + hx, sy, sz) - sample(sx - hx, sy, sz)) / (2.0f * hx);
           const float gy = (sample(sx, sy + hy, sz) - sample(sx, sy - hy, sz)) / (2.0f * hy);
@@ -221,10 +222,10 @@ __global__ __launch_bounds__(kDenseThreads, PHONG ? 4 : 5) void dense_march_kern
       active = active && !(e[3] < 0.0f);
       const float trn = active ? e[3] : 1.0f;
       const float ta = T * (1.0f - trn);
-      // (not by a weight of 0: behind the ray's end a shade may be infinite)
-      Cr = active ? fmaf(ta, e[0], Cr) : Cr;
-      Cg = active ? fmaf(ta, e[1], Cg) : Cg;
-      Cb = active ? fmaf(ta, e[2], Cb) : Cb;
+      // PHONG: not by a weight of 0, since behind the ray's end a shade may be infinite
+      Cr = active || !PHONG ? fmaf(ta, e[0], Cr) : Cr;
+      Cg = active || !PHONG ? fmaf(ta, e[1], Cg) : Cg;
+      Cb = active || !PHONG ? fmaf(ta, e[2], Cb) : Cb;
       A += ta;
       T *= trn;
       n += active ? 1 : 0;
@@ -816,7 +817,13 @@ int launch_render_dense(const float* vol, int nx, int ny, int nz, const TFDev& t
                        vb, m, out, stats, tx, ty, dt);
   };
   const bool big = (long long)nx * ny * nz >= (1ll << 29);  // 2^31 bytes
-  if (m.phong) big ? go(dense_march_kernel<true, true>) : go(dense_march_kernel<true, false>);
+  // (colours that are not finite are composited as a shade's are)
+  bool finite = true;
+  for (int q = 0; q < 4; ++q) {
+    finite = finite && std::isfinite(tf.base[q]);
+    for (int j = 0; j < tf.n_seg; ++j) finite = finite && std::isfinite(tf.delta[j][q]);
+  }
+  if (m.phong || !finite) big ? go(dense_march_kernel<true, true>) : go(dense_march_kernel<true, false>);
   else big ? go(dense_march_kernel<false, true>) : go(dense_march_kernel<false, false>);
   return check_launch();
 }

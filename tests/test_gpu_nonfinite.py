@@ -38,6 +38,25 @@ def test_dense_infinity_behind_the_surface(FV, w, h):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("eps", [0.0, 1e-3])
+def test_dense_infinite_colour(FV, eps):
+    """A transfer function whose red is infinite somewhere has no finite red anywhere
+    (0 * inf), but the other channels, and the pixels of rays that miss the box, are
+    those of a finite one."""
+    vol = np.zeros((24, 24, 24), np.float32)
+    vol[8:16, 8:16, 8:16] = 1.0
+    m, cam = I.March(step=1.0 / 3, ert_eps=eps), I.ortho_camera(40, 30)  # tiles with both kinds of rays
+    out = []
+    for red in (1.0, np.inf):
+        tf = I.TF(points=((0.0, 0.1, 0.2, 0.3, 0.0), (0.5, 0.1, 0.2, 0.3, 0.0), (1.0, red, 0.6, 0.2, 1.0)),
+                  opacity_scale=30.0)
+        out.append(FV.fvsrn_render_dense(torch.from_numpy(vol).cuda(), tf, [cam], m).cpu().numpy())
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0][..., 1:], out[1][..., 1:])
+    hit = np.abs((2.0 * np.arange(40) + 1.0) / 40 - 1.0) * 40 / 30 < 1.0  # columns of rays in the box
+    assert (out[1][:, :, ~hit] == 0.0).all() and (~hit).sum() >= 8
+    assert not np.isfinite(out[1][:, :, hit, 0]).any()
+
+
 @pytest.mark.parametrize("w,h", [(32, 24), (90, 60)])
 def test_render_infinity_behind_the_surface(FV, w, h):
     """The same for the network: latents of 3e38 in every other vertex layer from 0.27
