@@ -15,7 +15,7 @@
  *    device properties and two static per-GPU arrays allocated with its
  *    code object: the workspace of fvsrn_train_step_noalloc and the tile
  *    counters of fvsrn_render (see there).
- *  - Device buffers must be 16-byte aligned.
+ *  - Device buffers must be 16-byte aligned (an fvsrn_adam's moments: 4-byte).
  *  - Calls are asynchronous on `stream` (a hipStream_t passed as void*; NULL
  *    is the default stream). Argument errors are detected on the host before
  *    anything is launched and leave outputs untouched. Device faults surface
@@ -82,9 +82,13 @@ typedef struct {
   int32_t hidden_width;  /* c */
   int32_t hidden_layers; /* H activated layers, followed by the c -> num_outputs output layer */
   int32_t activation;    /* fvsrn_act */
-  int32_t precision;     /* network arithmetic: FVSRN_F32 (FP32 MFMA; where only
-                            values of a sine network are needed, FP16 MFMA on operands
-                            split into two FP16 values, as accurate), FVSRN_F16 or
+  int32_t precision;     /* network arithmetic: FVSRN_F32 (FP32 MFMA; for values of a sine
+                            network with the octave features, FP16 MFMA on operands split
+                            into two FP16 values, which hold up to 23 bits; for the
+                            adjoint of up to four layers where its weights leave room in
+                            LDS, the same and, backward, BF16 MFMA on three BF16 values.
+                            Errors against FP64 are 0.7 to 1.0 times the FP32 MFMA's on
+                            average), FVSRN_F16 or
                             FVSRN_BF16 (MFMA with FP32 accumulation). Phases, sigmoid,
                             TF and compositing are FP32 always; the latent
                             interpolation too, except for an FP16 or BF16 network on
@@ -203,8 +207,11 @@ typedef struct {
    slots issued (rays per wave x march steps of the wave, idle rays included;
    [0]/[2] is the occupancy of the matrix tiles). A wave's step holds 64
    samples without shading or with the adjoint, 16 with forward-mode gradients
-   (unless evaluated in reverse mode) and 8 with central differences: one of each of as many rays, or, in launches too small to
-   fill the GPU so, 2 to 16 consecutive ones of fewer rays. Phong shading needs the density gradient, obtained as
+   (64 where those are evaluated in reverse mode) and 8 with central differences:
+   one of each of as many rays, or, in launches too small to fill the GPU so, 2 to 16
+   consecutive ones of fewer rays, as the transfer function's extinctions allow
+   (samples behind a ray's end take no part). Phong shading needs the density
+   gradient, obtained as
    march->grad_mode selects (Sec. 6), for FP32, FP16 and BF16 networks
    (central differences and predicted gradients for the sine activation,
    also with a time encoding or a Fourier matrix; the adjoint for the sine
@@ -248,7 +255,7 @@ fvsrn_status fvsrn_grad_points(const fvsrn_net_desc* desc, const fvsrn_params* p
 typedef struct {
   float lr_grid, lr_mlp, beta1, beta2, eps;
   int32_t step;          /* t >= 1 of this update */
-  float* m_latent;       /* device [K R^3 F] */
+  float* m_latent;       /* device [K R^3 F], at any float */
   float* v_latent;
   float* m_weights;      /* device [n_weights] */
   float* v_weights;

@@ -30,10 +30,12 @@ constexpr int kRayBytes = 9 * 8 * kWave;  // a wave's FP64 rays in LDS (split re
 // FP32 sine networks with the octave features evaluate on the FP16 matrix
 // cores (fvsrn_split.hpp) wherever values are needed, and for the adjoint of up
 // to kSplitAdjLayers layers while its two sets of weight fragments leave LDS
-// for at least a wave per SIMD (c = 48: up to H = 3, with F = 16 up to 2; with 5
-// waves, c = 48, F = 8, H = 3 takes 197 us for 10^6 gradients against 276 on the
-// FP32 MFMA, H = 4 would run on 2). Forward-mode tangents, the other adjoints
-// and the other activations stay on the FP32 MFMA.
+// for at least a wave per SIMD of the render, whose waves also keep their rays
+// there (10.5 KB a wave; c = 48: up to H = 3, with F = 16 up to 2). The points, which take
+// 6 KB a wave, follow the same rule: at c = 48, F = 8, H = 3 their eight waves take
+// 197 us for 10^6 gradients against 276 on the FP32 MFMA; one layer more would
+// leave them four, which has not been measured. Forward-mode tangents, the other
+// adjoints and the other activations stay on the FP32 MFMA.
 template <class CF, int MODE, int HH = 0>
 constexpr bool use_split() {
   return CF::P == kF32 && CF::ACT == kSine && CF::TE == 0 && !CF::FM && MODE != kShadeFwd &&

@@ -335,8 +335,9 @@ __global__ void cast_bf16_kernel(const float* src, __bf16* dst, long long count)
 // neighbouring outputs, whose window rows share 14 inputs and their products.
 // Bound by its FP32 FMAs (1,815 per output): two 800 x 600 pairs 148 -> 67 us
 // against one thread per output reading both images through L1. The window's
-// sums keep their order (row by row): the variance terms cancel, so that taking
-// the rows' sums first (22 taps, 18 us) moves the map by 8e-5 of its norm.
+// sums are taken row by row over all 121 taps. Rows first, then columns (22 taps)
+// ran in 18 us; the variance terms cancel, so that it moves the map by 8e-5 of its
+// norm, in the one case measured to a third of this order's error against FP64.
 struct Window11 {
   float g[11];
 };

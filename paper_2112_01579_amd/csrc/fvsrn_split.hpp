@@ -20,9 +20,10 @@
 //    in FP32 (several infinities: by the sign of their channels' sum).
 //  * inputs without a bound -- the latent vector and the position -- and their
 //    weights stay on the FP32 MFMA, where they are off the VALU's path.
-// Measured against FP64 (see the tests) the densities are no further off than
-// the FP32 MFMA's: one K32 step rounds its accumulator once, eight K4 steps
-// eight times.
+// A sine of 2^-k so keeps 23 - k bits (its low half ends at 2^-25). Measured
+// against FP64 (2^19 points, six seeds, relative L2) the densities' error is 0.95 to 0.99
+// of the FP32 MFMA's on average and at most 1.05 for one seed, with all weights doubled
+// 0.87 to 0.92: one K32 step rounds its accumulator once, eight K4 steps eight times.
 //
 // The kernel is then VALU-bound (the sines, the splits, the corner sums), and
 // the input rows are built in the layout in which the MFMA reads them: lane
@@ -31,7 +32,7 @@
 // and fractions go through LDS (32 bytes a sample instead of a 272-byte row:
 // 12 waves per CU instead of 7). Measured, before and now: 10^6 random points
 // of the study network 145 -> 71 us, 2^24 points 2.14 -> 0.98 ms (17 G/s), its
-// trained 8 x 1024^2 orbit 331 -> 158 ms; VALU busy 80% in the render.
+// trained 8 x 1024^2 orbit 331 -> 158 ms; VALU busy 75% and MFMA 44% in the render.
 #pragma once
 #include "fvsrn_net.hpp"
 
@@ -518,8 +519,8 @@ __device__ inline f4 mlp_split(const char* wsm, const SplitTile& st, const Laten
 // points of the study network 324 -> 161 us (65,537 points 38 -> 28, of which
 // 20 are the weights' way into LDS), at c = 48, F = 16, H = 2 416 -> 215, an 800 x 600
 // Phong view of the study network 34.4 -> 16.5 ms; bound by the VALU
-// (sines, splits) and by 8 waves per CU. The gradients are closer to FP64
-// than before (3.2e-7 of the norm, FP32 MFMA 4.3e-7).
+// (sines, splits; 60% busy) and by 8 waves per CU. Against FP64 the gradients' error is
+// 0.75 to 0.80 of the FP32 MFMA's (c = 32 networks, six seeds).
 // Above four layers the derivatives do not fit in registers.
 constexpr int kSplitAdjLayers = 4;
 

@@ -1165,8 +1165,10 @@ __global__ __launch_bounds__(kTrainWavesPerBlock * 64) void fwd_bwd_h_kernel(
   }
   // ---------------- the wave's sums into its slice. (Not summed over the
   // workgroup first: that is 17 us faster per 2^18-point step, but weights that
-  // differ in their last bit after an update fall to other FP16 values, and
-  // the FP16 passes carry the order of these sums into later steps.)
+  // differ in their last bit after an update fall to other FP16 values, so that
+  // the next step's latent gradient moves by 1.5e-3 of its largest entry, against
+  // 5e-4 by the order of a cell's points alone. The error against FP64 of either
+  // order has not been compared.)
   if (wave >= n_waves) return;
 #pragma unroll
   for (int k = 0; k < NR0; ++k)
